@@ -1,0 +1,482 @@
+"""The workloads whose speed this repository watches, and their reference values.
+
+Each case is one call (or one short chain of calls) of the public Python
+binding, at the sizes that the benchmark, the corrector's training recipe and
+the tests use, with seeded synthetic images in place of photographs.  The
+listed cases cover the range from one small image to a batch of 64, both data
+types, even and odd numbers of orientations, sides that are no power of two,
+both schemes and projections, the restoration heuristics, the learned
+corrector's two directions and a plan that is made, used once and closed.
+
+``exact`` repeats a case in float64 torch: real FFTs, Crank-Nicolson by a
+cyclic tridiagonal solve of every mode or the matrix exponential of every
+frequency class, and the network as shifted matrix products.
+"""
+import math
+import os
+
+import numpy as np
+import torch
+
+import paper_1304_2062_amd
+
+DEV = "cuda"
+F64 = torch.float64
+WEIGHTS = os.path.join(os.path.dirname(os.path.abspath(paper_1304_2062_amd.__file__)), "corrector_N32.npz")
+CP = 32  # channels of the corrector's layers
+
+
+def listed():
+    return [
+        # one thumbnail: the smallest call, where launches and latency count
+        dict(name="inpaint_64_n16", kind="inpaint", M=64, N=16, dtype="f32", T=0.5, beta=1.0, n=50,
+             scheme="cn", proj="max", schedule="propagator", loss=0.30, stripes=0),
+        # the ordinary image: 512^2, 30 orientations, random loss and stripes
+        dict(name="inpaint_512_n30", kind="inpaint", M=512, N=30, dtype="f32", T=2.0, beta=1.0, n=200,
+             scheme="cn", proj="max", schedule="propagator", loss=0.70, stripes=32),
+        # the largest ordinary image and the benchmark's own size
+        dict(name="inpaint_2048_n32", kind="inpaint", M=2048, N=32, dtype="f32", T=4.0, beta=1.0, n=400,
+             scheme="cn", proj="max", schedule="propagator", loss=0.80, stripes=0),
+        # double precision, as a reference solve is asked for
+        dict(name="inpaint_1024_n32_f64", kind="inpaint", M=1024, N=32, dtype="f64", T=2.0, beta=1.0, n=200,
+             scheme="cn", proj="max", schedule="propagator", loss=0.60, stripes=0),
+        # an odd number of orientations on a side 4 * 3^4, exact scheme, mean projection
+        dict(name="inpaint_324_n15", kind="inpaint", M=324, N=15, dtype="f32", T=1.0, beta=1.0, n=100,
+             scheme="exact", proj="mean", schedule="propagator", loss=0.50, stripes=0),
+        # static restoration of a 256^2 image behind a stripe grid, 200 intervals
+        dict(name="restore_sr_256_n30", kind="restore", M=256, N=30, dtype="f32", alpha=2.0, Tp=0.8, n=200,
+             width=3, pct=37, dynamic=False),
+        # dynamic restoration in double precision, 160 intervals
+        dict(name="restore_dr_256_n30_f64", kind="restore", M=256, N=30, dtype="f64", alpha=0.30, Tp=4.0, n=160,
+             width=3, pct=37, dynamic=True),
+        # the steps one by one, for a program that works on the lifted volume itself
+        dict(name="steps_768_n24", kind="steps", M=768, N=24, dtype="f32", T=2.0, beta=1.0, n=200,
+             scheme="cn", proj="max", loss=0.60),
+        # 64 images of seven sides in one call
+        dict(name="batch_64", kind="batch", count=64, pick=1000, lo=128, hi=1024),
+        # the learned corrector applied to one volume
+        dict(name="corrector_1024", kind="cnn_forward", M=1024, B=1),
+        # the corrector's training direction: loss and gradients of a batch
+        dict(name="corrector_grad_256x16", kind="cnn_gradients", M=256, B=16),
+        # a plan made for one image: propagators, stencil taps, the solve, and the plan closed
+        dict(name="one_shot_384_n48", kind="one_shot", M=384, N=48, dtype="f32", T=1.0, beta=1.0, n=100,
+             scheme="cn", proj="max", schedule="propagator", loss=0.60, stripes=0),
+    ]
+
+
+def _sides(lo, hi):
+    return sorted(s for s in (2 ** a * 3 ** b for a in range(2, 12) for b in range(0, 7)) if lo <= s <= hi)
+
+
+def _log_pick(rng, values):
+    """One of the sorted values, spread over their logarithm."""
+    x = math.exp(rng.uniform(math.log(values[0]), math.log(values[-1])))
+    return min(values, key=lambda v: abs(math.log(v / x)))
+
+
+def draw(rng):
+    kind = rng.choice(["inpaint"] * 5 + ["restore"] * 2 + ["steps", "batch", "cnn_forward", "cnn_gradients", "one_shot"])
+    T = round(rng.uniform(0.5, 4.0), 3)
+    common = dict(T=T, beta=round(math.exp(rng.uniform(math.log(0.25), math.log(4.0))), 3),
+                  n=max(1, int(round(T / 0.01))), scheme=rng.choice(["cn", "cn", "cn", "exact"]),
+                  proj=rng.choice(["max", "max", "max", "mean"]), loss=round(rng.uniform(0.3, 0.85), 3))
+    if kind == "inpaint":
+        dtype = rng.choice(["f32", "f32", "f32", "f64"])
+        schedule = rng.choice(["propagator"] * 4 + ["iterated"])
+        N = rng.randint(6, 40)
+        if schedule == "iterated":
+            N, common["scheme"] = N + N % 2, "cn"
+        M = _log_pick(rng, _sides(48, 2048 if dtype == "f32" and N % 2 == 0 and N <= 32 and schedule == "propagator"
+                                  else 1024))
+        return dict(kind=kind, M=M, N=N, dtype=dtype, schedule=schedule, stripes=rng.choice([0, 0, 32]), **common)
+    if kind == "restore":
+        dynamic = rng.choice([False, False, True])
+        alpha, Tp, width, pct = rng.choice([(2.0, 0.8, 3, 37), (3.0, 0.2, 3, 37), (4.0, 0.2, 3, 37), (0.30, 4.0, 3, 37),
+                                            (0.33, 6.0, 8, 43), (0.33, 6.0, 10, 41)])
+        return dict(kind=kind, M=_log_pick(rng, _sides(96, 512)), N=2 * rng.randint(6, 16),
+                    dtype="f64" if dynamic else rng.choice(["f32", "f32", "f64"]), alpha=alpha, Tp=Tp,
+                    n=rng.randint(20, 100), width=width, pct=pct, dynamic=dynamic)
+    if kind == "steps":
+        common.pop("loss")
+        return dict(kind=kind, M=_log_pick(rng, _sides(64, 1024)), N=2 * rng.randint(4, 16),
+                    dtype=rng.choice(["f32", "f32", "f64"]), loss=0.6, **common)
+    if kind == "batch":
+        return dict(kind=kind, count=int(_log_pick(rng, list(range(2, 65)))), pick=rng.randint(0, 1 << 20),
+                    lo=rng.choice([64, 128]), hi=rng.choice([512, 1024]))
+    if kind == "cnn_forward":
+        return dict(kind=kind, M=_log_pick(rng, list(range(128, 1025, 16))), B=1)
+    if kind == "cnn_gradients":
+        return dict(kind=kind, M=_log_pick(rng, list(range(96, 257, 16))), B=rng.randint(1, 16))
+    return dict(kind="one_shot", M=_log_pick(rng, _sides(64, 768)), N=rng.randint(6, 48), dtype="f32",
+                schedule=rng.choice(["propagator", "auto"]), stripes=0, **common)
+
+
+# ---------------------------------------------------------------------------
+# Inputs
+# ---------------------------------------------------------------------------
+def _dtype(case):
+    return F64 if case["dtype"] == "f64" else torch.float32
+
+
+def _image(seed, M, shapes=24):
+    """A shaded image with edges and lines, float64 [M][M] in [0.02, 1], made on the GPU from the seed."""
+    g = np.random.Generator(np.random.PCG64([int(seed), M, 1]))
+    x = torch.arange(M, dtype=F64, device=DEV)
+    img = torch.full((M, M), 0.5, dtype=F64, device=DEV)
+    for _ in range(8):
+        u, v = (int(t) for t in g.integers(1, 9, size=2))
+        a, phi = 0.1 * g.uniform(0.2, 1.0), g.uniform(0, 2 * math.pi)
+        img += a * torch.sin(2 * math.pi * u * x[None, :] / M + 2 * math.pi * v * x[:, None] / M + phi)
+    shade = img.clone()
+    for k in range(shapes):
+        cx, cy = g.uniform(0, M, size=2)
+        dx = (x - cx + M / 2) % M - M / 2
+        dy = (x - cy + M / 2) % M - M / 2
+        t = g.uniform(0, math.pi)
+        c, s = math.cos(t), math.sin(t)
+        p = c * dx[None, :] + s * dy[:, None]
+        q = -s * dx[None, :] + c * dy[:, None]
+        level = g.uniform(0, 0.8)
+        if k % 2:  # a line of one to four pixels
+            d = q.abs() - g.uniform(0.5, 2.0)
+        else:      # a box
+            a, b = g.uniform(M / 32, M / 6, size=2)
+            d = torch.maximum(p.abs() - a, q.abs() - b)
+        cov = (0.5 - d).clamp_(0, 1)
+        img = img * (1 - cov) + (level + 0.2 * shade) * cov
+    return img.clamp_(0.02, 1.0)
+
+
+def _lost(seed, M, loss, stripes=0):
+    """The mask: random loss, and a 3-pixel stripe grid of period `stripes`."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(int(seed) * 1009 + M)
+    mask = torch.rand((M, M), generator=g, device=DEV) < loss
+    if stripes:
+        band = torch.arange(M, device=DEV) % stripes < 3
+        mask = mask | band[:, None] | band[None, :]
+    return mask.to(torch.uint8)
+
+
+def _stripe_grid(seed, M, width, pct):
+    p = int(round(width / (1.0 - math.sqrt(1.0 - pct / 100.0))))
+    g = np.random.Generator(np.random.PCG64([int(seed), M, 2]))
+    oy, ox = (int(v) for v in g.integers(0, p, size=2))
+    i = torch.arange(M, device=DEV)
+    return (((i + oy) % p < width)[:, None] | ((i + ox) % p < width)[None, :]).to(torch.uint8)
+
+
+def _batch_params(case):
+    """(M, N, T, n, loss) of each item, from the case alone: the batch is the same list for every seed."""
+    g = np.random.Generator(np.random.PCG64(case["pick"]))
+    sides = [s for s in (64, 96, 128, 192, 256, 384, 512, 768, 1024) if case["lo"] <= s <= case["hi"]]
+    out = []
+    for _ in range(case["count"]):
+        M, N = int(sides[g.integers(len(sides))]), int((16, 24, 32)[g.integers(3)])
+        T, loss = float(g.uniform(0.5, 4.0)), float(g.uniform(0.5, 0.85))
+        out.append((M, N, T, max(1, int(round(T / 0.01))), loss))
+    return out
+
+
+def _inputs(case, seed):
+    """The tensors of a case, without this repository's code."""
+    kind = case["kind"]
+    if kind in ("inpaint", "one_shot", "steps"):
+        M = case["M"]
+        return dict(f=_image(seed, M).to(_dtype(case)), mask=_lost(seed, M, case["loss"], case.get("stripes", 0)))
+    if kind == "restore":
+        M = case["M"]
+        return dict(f=(0.1 + 0.9 * _image(seed, M)).to(_dtype(case)),
+                    mask=_stripe_grid(seed, M, case["width"], case["pct"]))
+    if kind == "batch":
+        return dict(items=[dict(M=M, N=N, T=T, n=n, f=_image(seed * 4099 + i, M).float(),
+                                mask=_lost(seed * 4099 + i, M, loss))
+                           for i, (M, N, T, n, loss) in enumerate(_batch_params(case))])
+    # the corrector's volumes: lifted images after 25 coarse steps, and after 200 fine ones
+    M, B = case["M"], case["B"]
+    coarse, fine = [], []
+    for b in range(B):
+        f, mask = _image(seed * 4099 + b, M), _lost(seed * 4099 + b, M, 0.6)
+        fc = f * (1 - mask.double())
+        spec = torch.fft.rfft2(_lift(fc, _orient(fc, CP, 2.0), CP))
+        coarse.append(torch.fft.irfft2(_cn(spec, M, 2.0, 1.0, 25), s=(M, M)).float())
+        if kind == "cnn_gradients":
+            fine.append(torch.fft.irfft2(_propagate(spec, M, 2.0, 1.0, 200, "exact"), s=(M, M)).float())
+    out = dict(coarse=torch.stack(coarse))
+    if fine:
+        out["fine"] = torch.stack(fine)
+    return out
+
+
+def _restore_args(case):
+    beta = case["alpha"] * (case["N"] / (2 * math.pi)) ** 2
+    return case["Tp"] / 2, beta, case["n"], 0.5
+
+
+def prepare(case, seed):
+    from paper_1304_2062_amd import se2n
+    kind, s = case["kind"], dict(case=case, se2n=se2n)
+    s.update(_inputs(case, seed))
+    if kind in ("inpaint", "steps", "restore"):
+        plan = se2n.Plan(case["M"], case["N"], _dtype(case))
+        plan.set_schedule(case.get("schedule", "propagator"))
+        if kind == "restore":
+            T, beta, n, _ = _restore_args(case)
+            plan.precompute(T / n, beta, 1)
+            plan.restore_workspace()
+        else:
+            if case.get("schedule", "propagator") == "propagator":
+                plan.precompute(case["T"], case["beta"], case["n"], case["scheme"])
+            plan.workspace()
+        plan.orient_radius(2.0)
+        s["plan"] = plan
+    elif kind == "batch":
+        s["items"] = [se2n.BatchItem(it["f"], it["mask"], it["N"], it["T"], 1.0, it["n"]) for it in s["items"]]
+        s["ws"] = se2n.batch_workspace(s["items"])
+        se2n.inpaint_batched(s["items"], s["ws"])
+    elif kind in ("cnn_forward", "cnn_gradients"):
+        net = se2n.Corrector(CP)
+        net.set_params(_network(kind))
+        net.workspace(case["M"], case["B"], kind == "cnn_gradients")
+        s["net"] = net
+    return s
+
+
+def run(s):
+    case = s["case"]
+    kind = case["kind"]
+    if kind == "inpaint":
+        return s["plan"].inpaint(s["f"], s["mask"], case["T"], case["beta"], case["n"], scheme=case["scheme"],
+                                 proj=case["proj"])
+    if kind == "restore":
+        T, beta, n, eps = _restore_args(case)
+        return s["plan"].restore(s["f"], s["mask"], T, beta, n, eps, dynamic=case["dynamic"])
+    if kind == "steps":
+        plan = s["plan"]
+        rmap = plan.orient(s["f"], s["mask"])
+        psi = plan.lift(s["f"], s["mask"], rmap)
+        plan.diffuse(psi, case["T"], case["beta"], case["n"], case["scheme"])
+        return plan.project(psi, case["proj"]), psi, rmap
+    if kind == "batch":
+        return s["se2n"].inpaint_batched(s["items"], s["ws"])
+    if kind == "cnn_forward":
+        return s["net"].forward(s["coarse"])
+    if kind == "cnn_gradients":
+        return s["net"].gradients(s["coarse"], s["fine"])
+    plan = s["se2n"].Plan(case["M"], case["N"], _dtype(case))
+    plan.set_schedule(case["schedule"] if case["N"] % 2 == 0 else "propagator")
+    out = plan.inpaint(s["f"], s["mask"], case["T"], case["beta"], case["n"], scheme=case["scheme"], proj=case["proj"])
+    plan.close()
+    return out
+
+
+# ---------------------------------------------------------------------------
+# What a pass cannot do without
+# ---------------------------------------------------------------------------
+def _spectral_flops(M, N):
+    """Real 2-D FFTs of N slices there and back, and one N x N real system on every mode of the half spectrum
+    (two N/2 x N/2 ones for even N)."""
+    return 2 * N * 2.5 * M * M * math.log2(M * M) + M * M * N * N * (1 if N % 2 == 0 else 2)
+
+
+def work(case):
+    """Images in, images and maps out; the transforms and per-mode products of the method."""
+    kind = case["kind"]
+    if kind == "batch":
+        ps = _batch_params(case)
+        return dict(bytes=sum(10 * M * M for M, _, _, _, _ in ps), flops=sum(_spectral_flops(M, N) for M, N, _, _, _ in ps))
+    M = case["M"]
+    if kind in ("cnn_forward", "cnn_gradients"):
+        px = case["B"] * M * M
+        conv = 2 * 9 * CP * CP * px
+        if kind == "cnn_forward":
+            return dict(bytes=2 * CP * px * 4, flops=3 * conv)
+        return dict(bytes=2 * CP * px * 4, flops=8 * conv)
+    N, size = case["N"], 8 if case["dtype"] == "f64" else 4
+    if kind == "restore":
+        return dict(bytes=M * M * (2 * size + 4), flops=case["n"] * _spectral_flops(M, N))
+    if kind == "steps":  # the lifted volume is written, diffused in place and projected
+        return dict(bytes=M * M * (2 * size + 2 + 4 * N * size), flops=_spectral_flops(M, N))
+    return dict(bytes=M * M * (2 * size + 2), flops=_spectral_flops(M, N))
+
+
+# ---------------------------------------------------------------------------
+# The same in float64
+# ---------------------------------------------------------------------------
+def _orient(fc, N, sigma):
+    M = fc.shape[0]
+    k = torch.arange(M, dtype=F64, device=DEV)
+    kbar = (k + M // 2) % M - M // 2
+    gauss = torch.exp(-2 * math.pi ** 2 * sigma ** 2 * (kbar[None, :] ** 2 + kbar[:, None] ** 2) / M ** 2)
+    s = torch.sin(2 * math.pi * k / M) * math.sqrt(M)
+    F = torch.fft.fft2(fc)
+    gx = torch.fft.ifft2(F * (1j * s[None, :]) * gauss).real
+    gy = torch.fft.ifft2(F * (1j * s[:, None]) * gauss).real
+    theta = torch.atan2(gy, gx) + math.pi / 2
+    return torch.floor(theta * N / (2 * math.pi) + 0.5).to(torch.int64) % N
+
+
+def _lift(fc, rmap, N):
+    return torch.where(rmap[None] == torch.arange(N, device=DEV)[:, None, None], fc[None], torch.zeros((), dtype=F64, device=DEV))
+
+
+def _cn(spec, M, T, beta, n):
+    """n Crank-Nicolson steps of every mode of a half spectrum [N][M][M/2+1]: Thomas and Sherman-Morrison."""
+    N = spec.shape[0]
+    h = T / n / 2
+    s = torch.sin(2 * math.pi * torch.arange(M, dtype=F64, device=DEV) / M)
+    e = 2 * math.pi * torch.arange(N, dtype=F64, device=DEV) / N
+    a = torch.cos(e)[:, None, None] * s[None, None, :M // 2 + 1] + torch.sin(e)[:, None, None] * s[None, :, None]
+    V = 2 * beta + M * a * a
+    del a
+    b, off = 1 + h * V, -h * beta
+    g = -b[0]                       # the corners go into a rank-one term
+    d = b.clone()
+    d[0] -= g
+    d[N - 1] -= off * off / g
+    inv, cp = [1 / d[0]], []
+    for r in range(1, N):
+        cp.append(off * inv[r - 1])
+        inv.append(1 / (d[r] - off * cp[r - 1]))
+    del d, b
+
+    def solve(y):
+        for r in range(N):
+            y[r] = (y[r] if r == 0 else y[r] - off * y[r - 1]) * inv[r]
+        for r in range(N - 2, -1, -1):
+            y[r] -= cp[r] * y[r + 1]
+        return y
+
+    z = [torch.zeros_like(g) for _ in range(N)]
+    z[0], z[N - 1] = g.clone(), torch.full_like(g, off)
+    z = solve(z)
+    w = off / g                     # v = (1, 0, ..., 0, off / g)
+    den = 1 / (1 + z[0] + w * z[N - 1])
+    x = list(spec.clone())
+    for _ in range(n):
+        y = solve([x[r] + h * (beta * (x[(r + 1) % N] + x[r - 1]) - V[r] * x[r]) for r in range(N)])
+        c = (y[0] + w * y[N - 1]) * den
+        x = [y[r] - c * z[r] for r in range(N)]
+    return torch.stack(x)
+
+
+def _class_exp(M, N, T, beta):
+    """exp(T A) of every class (|s_kx|, |s_ky|), [Q][Q][N][N]; the symbols are those of lx, ly = 0 .. M/4."""
+    s = torch.sin(2 * math.pi * torch.arange(M // 4 + 1, dtype=F64, device=DEV) / M)
+    e = 2 * math.pi * torch.arange(N, dtype=F64, device=DEV) / N
+    a = torch.cos(e) * s[:, None, None] + torch.sin(e) * s[None, :, None]
+    L = -2 * torch.eye(N, dtype=F64, device=DEV)
+    i = torch.arange(N, device=DEV)
+    L[i, (i + 1) % N] += 1
+    L[i, (i - 1) % N] += 1
+    out = torch.empty(a.shape[0], a.shape[0], N, N, dtype=F64, device=DEV)
+    for x in range(a.shape[0]):
+        out[x] = torch.linalg.matrix_exp(T * (beta * L - torch.diag_embed(M * a[x] * a[x])))
+    return out
+
+
+def _apply_classes(P, spec, M):
+    """Every mode of a half spectrum times its class's matrix; where s_kx s_ky < 0 the orientations are mirrored."""
+    N = spec.shape[0]
+    k = torch.arange(M, device=DEV)
+    fold = torch.minimum(k % (M // 2), M // 2 - k % (M // 2))
+    mirror = (N - torch.arange(N, device=DEV)) % N
+    flip = (k > M // 2)[:, None, None]
+    out = torch.empty_like(spec)
+    for kx in range(M // 2 + 1):
+        x = spec[:, :, kx].t()
+        x = torch.view_as_real(torch.where(flip[:, :, 0], x[:, mirror], x).contiguous())
+        y = torch.view_as_complex(torch.matmul(P[int(fold[kx])][fold], x).contiguous())
+        out[:, :, kx] = torch.where(flip[:, :, 0], y[:, mirror], y).t()
+    return out
+
+
+def _propagate(spec, M, T, beta, n, scheme):
+    if scheme == "exact":
+        return _apply_classes(_class_exp(M, spec.shape[0], T, beta), spec, M)
+    return _cn(spec, M, T, beta, n)
+
+
+def _inpaint_exact(f, mask, N, T, beta, n, scheme, proj):
+    M = f.shape[0]
+    fc = f.double() * (1 - mask.double())
+    psi = torch.fft.irfft2(_propagate(torch.fft.rfft2(_lift(fc, _orient(fc, N, 2.0), N)), M, T, beta, n, scheme), s=(M, M))
+    return (psi.amax(0) if proj == "max" else psi.mean(0)), psi
+
+
+def _restore_exact(case, f, mask):
+    M, N = case["M"], case["N"]
+    T, beta, n, eps = _restore_args(case)
+    fc = f.double() * (1 - mask.double())
+    psi = _lift(fc, _orient(fc, N, 2.0), N)
+    good = mask == 0
+    href = psi.amax(0)
+    for i in range(n):
+        if i:
+            h = psi.amax(0)
+            if case["dynamic"]:
+                near, total, count = torch.zeros_like(good), torch.zeros_like(h), torch.zeros_like(h)
+                for dy in (-1, 0, 1):
+                    for dx in (-1, 0, 1):
+                        gs = torch.roll(good, (dy, dx), (0, 1))
+                        near |= gs
+                        count += (~gs).double()
+                        total += torch.where(gs, torch.zeros_like(h), torch.roll(h, (dy, dx), (0, 1)))
+                new = ~good & near & (h > total / count.clamp_min(1))
+                href = torch.where(new, h, href)
+                good = good | new
+            mix = good & (h > 0)
+            psi = psi * torch.where(mix, (eps * href + (1 - eps) * h) / torch.where(mix, h, torch.ones_like(h)), torch.ones_like(h))
+        psi = torch.fft.irfft2(_cn(torch.fft.rfft2(psi), M, T / n, beta, 1), s=(M, M))
+    return psi.amax(0), None, None
+
+
+def _network(kind):
+    """The trained parameters; for the training direction those of an early step (He-normal layers, a small last one:
+    at the minimum itself the gradient is the rounding of its cancelling terms)."""
+    if kind == "cnn_forward":
+        with np.load(WEIGHTS, allow_pickle=False) as z:
+            return np.array(z["params"], dtype=np.float32)
+    g = np.random.Generator(np.random.PCG64(11))
+    layers = [np.concatenate([g.standard_normal(CP * CP * 9) * scale * math.sqrt(2 / (9 * CP)), np.zeros(CP)])
+              for scale in (1.0, 1.0, 0.3)]
+    return np.concatenate(layers).astype(np.float32)
+
+
+def _net_forward(p, x):
+    """x [C][B][M][M] -> the corrected volumes, float64, one normalisation per image."""
+    s = x.square().mean((0, 2, 3)).sqrt()
+    s = torch.where(s > 0, s, torch.ones_like(s))[None, :, None, None]
+    a, per = x / s, CP * CP * 9 + CP
+    for layer in range(3):
+        w = p[layer * per:layer * per + CP * CP * 9].view(CP, CP, 9)
+        z = p[layer * per + CP * CP * 9:(layer + 1) * per].view(CP, 1).expand(CP, a[0].numel())
+        for tap in range(9):
+            shifted = torch.roll(a, (1 - tap // 3, 1 - tap % 3), (2, 3)).reshape(CP, -1)
+            z = z + w[:, :, tap].contiguous() @ shifted
+        a = z.view(a.shape)
+        if layer < 2:
+            a = torch.relu(a)
+    return x + s * a, s
+
+
+def exact(case, seed):
+    kind, x = case["kind"], _inputs(case, seed)
+    if kind in ("inpaint", "one_shot", "steps"):
+        out, psi = _inpaint_exact(x["f"], x["mask"], case["N"], case["T"], case["beta"], case["n"], case["scheme"],
+                                  case["proj"])
+        return (out, psi, None) if kind == "steps" else (out, None)
+    if kind == "restore":
+        return _restore_exact(case, x["f"], x["mask"])
+    if kind == "batch":
+        return [_inpaint_exact(it["f"], it["mask"], it["N"], it["T"], 1.0, it["n"], "cn", "max")[0] for it in x["items"]]
+    p = torch.from_numpy(_network(kind).astype(np.float64)).to(DEV)
+    v = x["coarse"].double().transpose(0, 1)
+    if kind == "cnn_forward":
+        with torch.no_grad():
+            return _net_forward(p, v)[0].transpose(0, 1)
+    p.requires_grad_(True)
+    out, s = _net_forward(p, v)
+    loss = ((out - x["fine"].double().transpose(0, 1)) / s).square().mean()
+    loss.backward()
+    return p.grad, loss.detach().reshape(1)
