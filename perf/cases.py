@@ -91,8 +91,8 @@ def draw(rng):
         return dict(kind=kind, M=M, N=N, dtype=dtype, schedule=schedule, stripes=rng.choice([0, 0, 32]), **common)
     if kind == "restore":
         dynamic = rng.choice([False, False, True])
-        alpha, Tp, width, pct = rng.choice([(2.0, 0.8, 3, 37), (3.0, 0.2, 3, 37), (4.0, 0.2, 3, 37), (0.30, 4.0, 3, 37),
-                                            (0.33, 6.0, 8, 43), (0.33, 6.0, 10, 41)])
+        # weights and times of the rows that stay bounded at these numbers of intervals
+        alpha, Tp, width, pct = rng.choice([(2.0, 0.8, 3, 37), (3.0, 0.2, 3, 37), (4.0, 0.2, 3, 37)])
         return dict(kind=kind, M=_log_pick(rng, _sides(96, 512)), N=2 * rng.randint(6, 16),
                     dtype="f64" if dynamic else rng.choice(["f32", "f32", "f64"]), alpha=alpha, Tp=Tp,
                     n=rng.randint(20, 100), width=width, pct=pct, dynamic=dynamic)
