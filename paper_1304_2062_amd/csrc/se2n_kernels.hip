@@ -22,6 +22,7 @@
 
 #include "se2n_fft.hpp"
 #include "se2n_internal.hpp"
+#include "se2n_pair.hpp"
 #include "se2n_passes.hpp"
 
 namespace se2n {
@@ -226,8 +227,10 @@ __device__ void lds_copy(const double* A, double* B, int n, int tid) {
 // the padding of the flag rows the slot ends (by the thread group of one
 // workgroup; tid < 64).
 template <class R>
-__device__ void store_class_flags(R* Ptab, int M, int N, int Q, int FS, int lx, int ly, bool negligible, int tid) {
-    uint8_t* flags = reinterpret_cast<uint8_t*>(Ptab + table_slots(M, N) * (size_t)table_class_stride(N, (int)sizeof(R)));
+__device__ void store_class_flags(R* Ptab, int M, int N, int Q, int FS, int lx, int ly, bool negligible, int tid,
+                                  int pair) {
+    uint8_t* flags = reinterpret_cast<uint8_t*>(
+        Ptab + (pair ? pair_table_entries(M, N) : table_slots(M, N) * (size_t)table_class_stride(N, (int)sizeof(R))));
     if (tid == 0) {
         flags[(size_t)lx * FS + ly] = negligible ? 1 : 0;
         if (table_sym(N)) flags[(size_t)ly * FS + lx] = negligible ? 1 : 0;
@@ -236,10 +239,37 @@ __device__ void store_class_flags(R* Ptab, int M, int N, int Q, int FS, int lx, 
         for (int j = Q + tid; j < FS; j += 64) flags[(size_t)lx * FS + j] = 0;
 }
 
+// The element-major table of the pair path: block b of class (lx, ly), and
+// with 4 | N of class (ly, lx), whose block is the same one conjugated by the
+// reflection r -> N/4 - r (an index that wraps around turns the sign of an
+// antiperiodic slice).  at(i, j) is the symmetrised entry of this class.
+template <class R, class F>
+__device__ void store_pair_block(R* Ptab, int M, int N, int b, int lx, int ly, int h, double scale, int tid, F&& at) {
+    const int Eh = h * (h + 1) / 2;
+    const int QP = pair_qp(M);
+    const int nblk = pair_nblk(N);
+    R* d0 = Ptab + ((size_t)(lx * nblk + b) * Eh) * QP + ly;
+    R* d1 = Ptab + ((size_t)(ly * nblk + b) * Eh) * QP + lx;
+    const bool both = table_sym(N) && lx != ly;
+    const int g = N / 4;
+    for (int idx = tid; idx < h * h; idx += 64) {
+        const int i = idx / h;
+        const int j = idx - i * h;
+        if (j < i) continue;
+        const size_t e = (size_t)(i * h - i * (i - 1) / 2 + (j - i)) * QP;
+        d0[e] = (R)(at(i, j) * scale);
+        if (both) {
+            const int a = i > g ? g - i + h : g - i, c = j > g ? g - j + h : g - j;
+            const double u = at(a, c) * scale;
+            d1[e] = (R)(b == 1 && (i > g) != (j > g) ? -u : u);
+        }
+    }
+}
+
 template <class R>
 __global__ __launch_bounds__(64) void k_precompute(R* __restrict__ Ptab, int M, int N, int Q, int FS,
                                                    double beta, double T, int nsteps, int scheme,
-                                                   double scale, int keep_all) {
+                                                   double scale, int keep_all, int pair) {
     extern __shared__ double sm[];
     const bool odd = (N & 1) != 0;
     const int h = odd ? N : N / 2;
@@ -381,18 +411,21 @@ __global__ __launch_bounds__(64) void k_precompute(R* __restrict__ Ptab, int M, 
                 const int e = blk * Eh + i * h - i * (i - 1) / 2 + (j - i);
                 const double u = 0.5 * (Rs[i * h + j] + Rs[j * h + i]);
                 pmax = fmax(pmax, fabs(u));
-                dst[e] = (R)(u * scale);
+                if (!pair) dst[e] = (R)(u * scale);
             }
         }
+        if (pair)
+            store_pair_block<R>(Ptab, M, N, blk, lx, ly, h, scale, tid,
+                                [&](int i, int j) { return 0.5 * (Rs[i * h + j] + Rs[j * h + i]); });
         __syncthreads();
     }
     // negligible-class flag (the workgroup is one wavefront): set when every
     // entry of both blocks is below 2^-30 (FP32) or 2^-60 (FP64); the solve
     // then writes zeros for the class's modes without reading them
     for (int off = 32; off >= 1; off >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, off, 64));
-    store_class_flags<R>(Ptab, M, N, Q, FS, lx, ly, !keep_all && pmax < (sizeof(R) == 4 ? 0x1p-30 : 0x1p-60), tid);
+    store_class_flags<R>(Ptab, M, N, Q, FS, lx, ly, !keep_all && pmax < (sizeof(R) == 4 ? 0x1p-30 : 0x1p-60), tid, pair);
     // the class's line padding
-    for (int e = E + tid; e < CS; e += 64) Ptab[(size_t)blockIdx.x * CS + e] = R(0);
+    if (!pair) for (int e = E + tid; e < CS; e += 64) Ptab[(size_t)blockIdx.x * CS + e] = R(0);
 }
 
 // ---------------------------------------------------------------------------
@@ -441,7 +474,7 @@ __device__ __forceinline__ void mm16_pair(const double* X0, const double* Y0, do
 template <class R>
 __global__ __launch_bounds__(64) void k_precompute_mfma(R* __restrict__ Ptab, int M, int N, int Q, int FS,
                                                         double beta, double T, int nsteps, int scheme, double scale,
-                                                        int keep_all) {
+                                                        int keep_all, int pair) {
     __shared__ double sm[6 * kMM];
     __shared__ double spot[16];
     const int l = threadIdx.x;
@@ -576,12 +609,20 @@ __global__ __launch_bounds__(64) void k_precompute_mfma(R* __restrict__ Ptab, in
             const double* Rb = sm + Ro + b * kMM;
             const double u = 0.5 * (Rb[i * kMS + j] + Rb[j * kMS + i]);
             pmax = fmax(pmax, fabs(u));
-            dst[b * Eh + i * h - i * (i - 1) / 2 + (j - i)] = (R)(u * scale);
+            if (!pair) dst[b * Eh + i * h - i * (i - 1) / 2 + (j - i)] = (R)(u * scale);
+        }
+    }
+    if (pair) {
+        for (int b = 0; b < 2; ++b) {
+            const double* Rb = sm + Ro + b * kMM;
+            store_pair_block<R>(Ptab, M, N, b, lx, ly, h, scale, l,
+                                [&](int i, int j) { return 0.5 * (Rb[i * kMS + j] + Rb[j * kMS + i]); });
         }
     }
     for (int off = 32; off >= 1; off >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, off, 64));
-    store_class_flags<R>(Ptab, M, N, Q, FS, lx, ly, !keep_all && pmax < (sizeof(R) == 4 ? 0x1p-30 : 0x1p-60), l);
-    for (int e = 2 * Eh + l; e < CS; e += 64) dst[e] = R(0);
+    store_class_flags<R>(Ptab, M, N, Q, FS, lx, ly, !keep_all && pmax < (sizeof(R) == 4 ? 0x1p-30 : 0x1p-60), l, pair);
+    if (!pair)
+        for (int e = 2 * Eh + l; e < CS; e += 64) dst[e] = R(0);
 }
 
 // ---------------------------------------------------------------------------
@@ -840,7 +881,7 @@ hipError_t launch_project(const R* psi, R* out, int M, int N, bool mean, hipStre
 
 template <class R>
 hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int nsteps, int scheme,
-                             hipStream_t st, bool keep_all) {
+                             hipStream_t st, bool keep_all, bool pair) {
     const int Q = M / 4 + 1;
     const size_t slots = table_slots(M, N);  // one workgroup per stored class
     const int h = (N & 1) ? N : N / 2;
@@ -852,12 +893,12 @@ hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int n
     // faster on the scalar path); SE2N_SCALAR_PRECOMPUTE forces the scalar one
     if (!(N & 1) && h > 8 && h <= 16 && std::getenv("SE2N_SCALAR_PRECOMPUTE") == nullptr) {
         hipLaunchKernelGGL((k_precompute_mfma<R>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
-                           flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0);
+                           flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_precompute<R>), dim3((unsigned)slots), dim3(64), lds, st, Ptab, M, N, Q,
                        flag_stride(M), beta,
-                       T, nsteps, scheme, scale, keep_all ? 1 : 0);
+                       T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -881,7 +922,7 @@ hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int n
     template hipError_t launch_lift<R>(const R*, const uint8_t*, const uint8_t*, R*, int, int,         \
                                        hipStream_t);                                                   \
     template hipError_t launch_project<R>(const R*, R*, int, int, bool, hipStream_t);                  \
-    template hipError_t launch_precompute<R>(R*, int, int, double, double, int, int, hipStream_t, bool);
+    template hipError_t launch_precompute<R>(R*, int, int, double, double, int, int, hipStream_t, bool, bool);
 
 SE2N_INSTANTIATE(float)
 SE2N_INSTANTIATE(double)

@@ -21,6 +21,7 @@
 #include "../../include/se2n.h"
 #include "se2n_internal.hpp"
 #include "se2n_host.hpp"
+#include "se2n_pair.hpp"
 
 using namespace se2n;
 
@@ -310,8 +311,19 @@ struct se2n_plan_s {
     size_t restore_workspace() const {
         return workspace() + vol_bytes() + 2 * enc_bytes() + align256((size_t)M * M * sizeof(int16_t));
     }
-    // class-major propagators + one flag byte per class (padded rows)
-    size_t table_bytes() const { return se2n::table_bytes(M, N, (int)real_size()); }
+    // propagators + one flag byte per class (padded rows): class-major, or
+    // element-major on the pair path
+    size_t table_bytes() const {
+        return pair ? pair_table_bytes(M, N, (int)real_size()) : se2n::table_bytes(M, N, (int)real_size());
+    }
+    const uint8_t* flags_of(const void* P) const {
+        return pair ? (const uint8_t*)P + pair_table_entries(M, N) * real_size()
+                    : table_flags(P, M, N, (int)real_size());
+    }
+    // the propagator schedule runs on the pair path (se2n_pair.hpp): three
+    // passes instead of five (SE2N_NO_PAIR at plan creation: the five)
+    bool pair = false;
+    PairGeom pg{};
 };
 
 namespace {
@@ -460,10 +472,11 @@ int get_propagators(se2n_plan p, double T, double beta, int n_steps, se2n_scheme
     {
         ProfScope ps(p, "precompute", st);
         if (p->dt == SE2N_F32)
-            e = launch_precompute<float>((float*)d, p->M, p->N, beta, T, n_steps, (int)scheme, st, p->keep_negligible);
+            e = launch_precompute<float>((float*)d, p->M, p->N, beta, T, n_steps, (int)scheme, st, p->keep_negligible,
+                                         p->pair);
         else
             e = launch_precompute<double>((double*)d, p->M, p->N, beta, T, n_steps, (int)scheme, st,
-                                          p->keep_negligible);
+                                          p->keep_negligible, p->pair);
     }
     if (e != hipSuccess) {
         (void)hipFree(d);
@@ -657,6 +670,34 @@ int project_spec(se2n_plan p, const C2<R>* spec, bool blocked, typename Enc<R>::
     return SE2N_OK;
 }
 
+// The pair path's passes (se2n_pair.hpp).
+template <class R>
+int pair_lift(se2n_plan p, const R* f, const uint8_t* mask, const uint8_t* rmap, C2<R>* spec, hipStream_t st) {
+    SE2N_TIMED(p, "lift_row_fwd", st,
+               launch_pair_fwd<R>(PSRC_LIFT, f, mask, rmap, nullptr, spec, p->M, p->N, p->pg, p->planM,
+                                  (const C2<R>*)p->tw, st),
+               "lift + row FFT");
+    return SE2N_OK;
+}
+
+template <class R>
+int pair_middle(se2n_plan p, C2<R>* spec, const void* P, hipStream_t st) {
+    SE2N_TIMED(p, "col_solve", st,
+               launch_pair_mid<R>(spec, (const R*)P, p->M, p->N, p->pg, p->planM, (const C2<R>*)p->tw, st),
+               "column FFT, per-mode solve and inverse column FFT");
+    return SE2N_OK;
+}
+
+template <class R>
+int pair_project(se2n_plan p, C2<R>* spec, se2n_proj mode, R* out, hipStream_t st) {
+    const bool mean = mode == SE2N_PROJ_MEAN;
+    SE2N_TIMED(p, mean ? "row_inv_mean" : "row_inv_max", st,
+               launch_pair_inv<R>(mean ? PDST_SUM : PDST_MAX, spec, out, p->M, p->N, p->pg, p->planM,
+                                  (const C2<R>*)p->tw, st),
+               "inverse row pass");
+    return SE2N_OK;
+}
+
 template <class R>
 int inpaint_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, double T, double beta,
                  int n_steps, se2n_scheme scheme, se2n_proj mode, const uint8_t* rmap_in, uint8_t* rmap_out,
@@ -678,6 +719,11 @@ int inpaint_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
                  "copy of rmap_in to rmap_out");
     }
     const C2<R>* tw = (const C2<R>*)p->tw;
+    if (p->pair && !iter) {
+        rc = pair_lift<R>(p, f, mask, rmap, w.spec, st);
+        if (!rc) rc = pair_middle<R>(p, w.spec, P, st);
+        return rc ? rc : pair_project<R>(p, w.spec, mode, out, st);
+    }
     SE2N_TIMED(p, "lift_row_fwd", st,
                launch_row_fwd<R>(SRC_LIFT, f, mask, rmap, nullptr, w.spec, p->M, p->N, p->geom, p->planH, tw, st),
                "lift + row FFT");
@@ -697,6 +743,18 @@ int diffuse_impl(se2n_plan p, R* psi, double T, double beta, int n_steps, se2n_s
     p->last_schedule = iter ? SE2N_SCHEDULE_ITERATED : SE2N_SCHEDULE_PROPAGATOR;
     Ws<R> w = split_workspace<R>(p, workspace);
     const C2<R>* tw = (const C2<R>*)p->tw;
+    if (p->pair && !iter) {
+        SE2N_TIMED(p, "row_fwd", st,
+                   launch_pair_fwd<R>(PSRC_VOLUME, nullptr, nullptr, nullptr, psi, w.spec, p->M, p->N, p->pg, p->planM,
+                                      tw, st),
+                   "row FFT");
+        rc = pair_middle<R>(p, w.spec, P, st);
+        if (rc) return rc;
+        SE2N_TIMED(p, "row_inv_volume", st,
+                   launch_pair_inv<R>(PDST_VOLUME, w.spec, psi, p->M, p->N, p->pg, p->planM, tw, st),
+                   "inverse row FFT");
+        return SE2N_OK;
+    }
     SE2N_TIMED(p, "row_fwd", st,
                launch_row_fwd<R>(SRC_VOLUME, nullptr, nullptr, nullptr, psi, w.spec, p->M, p->N, p->geom,
                                  p->planH, tw, st),
@@ -742,10 +800,29 @@ int restore_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
     }
     const C2<R>* tw = (const C2<R>*)p->tw;
     if (dynamic) SE2N_TIMED(p, "dr_init", st, launch_dr_init<R>(join, href, f, mask, p->M, st), "DR set-up");
-    SE2N_TIMED(p, "lift_row_fwd", st,
-               launch_row_fwd<R>(SRC_LIFT, f, mask, rmap, nullptr, w.spec, p->M, p->N, p->geom, p->planH, tw, st),
-               "lift + row FFT");
+    if (p->pair) {
+        rc = pair_lift<R>(p, f, mask, rmap, w.spec, st);
+        if (rc) return rc;
+    } else {
+        SE2N_TIMED(p, "lift_row_fwd", st,
+                   launch_row_fwd<R>(SRC_LIFT, f, mask, rmap, nullptr, w.spec, p->M, p->N, p->geom, p->planH, tw, st),
+                   "lift + row FFT");
+    }
     for (int i = 0; i < n_int; ++i) {
+        if (p->pair) {
+            // a mesh point on whole rows of every pair in LDS
+            if (i > 0 && dynamic)
+                SE2N_TIMED(p, "dr_step", st,
+                           launch_pair_dr<R>(w.spec, vol, h, join, href, eps, i, p->M, p->N, p->pg, p->planM, tw, st),
+                           "DR growth and mix between row FFTs");
+            else if (i > 0)
+                SE2N_TIMED(p, "sr_mix", st,
+                           launch_pair_sr<R>(w.spec, f, mask, eps, p->M, p->N, p->pg, p->planM, tw, st),
+                           "SR mix between row FFTs");
+            rc = pair_middle<R>(p, w.spec, P, st);
+            if (rc) return rc;
+            continue;
+        }
         if (i > 0) {
             SE2N_TIMED(p, "row_inv_volume", st,
                        launch_row_inv<R>(DST_VOLUME, w.rows(), vol, nullptr, nullptr, p->M, p->N, p->N, R(1), p->geom,
@@ -764,7 +841,8 @@ int restore_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
         rc = spectral_middle<R>(p, w.spec, w.blk, P, st);
         if (rc) return rc;
     }
-    rc = project_spec<R>(p, w.rows(), w.blk != nullptr, w.enc, mode, out, st);
+    rc = p->pair ? pair_project<R>(p, w.spec, mode, out, st)
+                 : project_spec<R>(p, w.rows(), w.blk != nullptr, w.enc, mode, out, st);
     if (rc) return rc;
     if (join_out) {
         if (dynamic)
@@ -857,6 +935,8 @@ int se2n_plan_create(se2n_plan* out, int M, int N, se2n_dtype dtype) {
         delete p;
         return rc;
     }
+    p->pair = pair_fits(M, N, (int)p->real_size()) && std::getenv("SE2N_NO_PAIR") == nullptr;
+    if (p->pair) p->pg = pair_geom(M, N, (int)p->real_size(), num_cu);
     *out = p;
     return SE2N_OK;
 }
@@ -918,9 +998,8 @@ int se2n_propagator_flags(se2n_plan p, double T, double beta, int n_steps, se2n_
     hipStream_t st = (hipStream_t)stream;
     rc = get_propagators(p, T, beta, n_steps, scheme, st, &P);
     if (rc) return rc;
-    const int rs = (int)p->real_size();
     const size_t FS = (size_t)flag_stride(p->M);
-    const uint8_t* dflags = table_flags(P, p->M, p->N, rs);
+    const uint8_t* dflags = p->flags_of(P);
     // the precompute ran on `st`; copy the padded rows synchronously, then unpad
     SE2N_HIP(hipStreamSynchronize(st), "hipStreamSynchronize before the flag copy");
     std::vector<uint8_t> rows((size_t)q * FS);
