@@ -252,8 +252,9 @@ __device__ void store_pair_block(R* Ptab, int M, int N, int b, int lx, int ly, i
     R* d1 = Ptab + ((size_t)(ly * nblk + b) * Eh) * QP + lx;
     const bool both = table_sym(N) && lx != ly;
     const int g = N / 4;
+    const float inv_h = 1.0f / (float)h;
     for (int idx = tid; idx < h * h; idx += 64) {
-        const int i = idx / h;
+        const int i = fdiv(idx, inv_h);
         const int j = idx - i * h;
         if (j < i) continue;
         const size_t e = (size_t)(i * h - i * (i - 1) / 2 + (j - i)) * QP;
@@ -430,199 +431,259 @@ __global__ __launch_bounds__(64) void k_precompute(R* __restrict__ Ptab, int M, 
 
 // ---------------------------------------------------------------------------
 // Propagator precompute on the FP64 matrix cores, for blocks of at most
-// 16 x 16 (even N <= 32): one wavefront per frequency class, both blocks.
+// 32 x 32 (even N; odd N up to 32, whose one block is the whole propagator):
+// one wavefront per frequency class.
 // ---------------------------------------------------------------------------
-// Each block is embedded in a 16 x 16 matrix (the padding is the identity,
-// which every step below keeps, and is never stored).  Matrices live in LDS
-// row-major with a row stride of 17 doubles, so that the 16 lanes reading a
-// column touch 16 distinct bank pairs.
-//   CN:    the left matrix I - tau A / 2 is cyclic tridiagonal; lane c of
-//          block b solves it for the unit vector e_c (Thomas elimination with
-//          a Sherman-Morrison correction for the corners, as the paper's
-//          remark 2 suggests for the time steps themselves), and the
-//          one-step propagator is C = (I - tau A/2)^{-1} (I + tau A/2)
+// A block is embedded in TILES x TILES tiles of 16 x 16 (zero padding).  The
+// result D[i][j] of v_mfma_f64_16x16x4 lies in lane j + 16 (i mod 4), element
+// i div 4; its operands are A[i][k] in lane i + 16 k and B[k][j] in lane
+// j + 16 k.  So element kk of a result is, as it stands, the B operand of
+// k-step kk, and for a symmetric matrix also the A operand: every matrix here
+// is a polynomial of the symmetric generator, so products feed products from
+// registers, with no LDS and no barrier in the powering.  Bound by the chain
+// of dependent products of each wavefront (FP32 tables, against operands
+// through LDS for blocks of 9..16 and scalar products for the others):
+// 1024^2, N = 32, 200 steps 278 -> 216 us, 384^2, N = 48, 100 steps 900 -> 145,
+// N = 64 3276 -> 180, 256^2, N = 31, 200 steps 1325 -> 98.  Rounding leaves
+// R = C^n asymmetric by a few ulps; the stored entries are symmetrised.
+//   CN:    the left matrix I - tau A / 2 is cyclic tridiagonal: one lane per
+//          block factors it (Thomas elimination with a Sherman-Morrison
+//          correction for the corners, as the paper's remark 2 suggests for
+//          the time steps themselves), lane c solves for the unit vector e_c,
+//          and the one-step propagator is C = (I - tau A/2)^{-1} (I + tau A/2)
 //          = 2 (I - tau A/2)^{-1} - I.  P = C^n by binary powering.
 //   EXACT: P = e^{T A} by scaling and squaring of a degree-16 Taylor sum.
-// A 16 x 16 x 16 product is four v_mfma_f64_16x16x4 (A[i][k] from lane
-// i + 16 k, B[k][j] from lane j + 16 k; D[i][j] comes back in lane
-// j + 16 (i mod 4), element i div 4); the two blocks' products are issued
-// interleaved.
 typedef double mf64x4 __attribute__((ext_vector_type(4)));
-constexpr int kMS = 17;            // LDS row stride of a 16 x 16 matrix
-constexpr int kMM = 16 * kMS;      // doubles per matrix
 
-// D_b = X_b Y_b for b = 0, nb - 1 (X, Y, D: per-block matrix pointers).
-__device__ __forceinline__ void mm16_pair(const double* X0, const double* Y0, double* D0, const double* X1,
-                                          const double* Y1, double* D1, int nb, int l) {
-    const int i = l & 15, q = l >> 4;
-    mf64x4 c0 = {0.0, 0.0, 0.0, 0.0}, c1 = {0.0, 0.0, 0.0, 0.0};
+template <int TILES>
+struct RegMat {
+    mf64x4 t[TILES][TILES];
+    __device__ __forceinline__ void zero() {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-        const int k = 4 * kk + q;
-        c0 = __builtin_amdgcn_mfma_f64_16x16x4f64(X0[i * kMS + k], Y0[k * kMS + i], c0, 0, 0, 0);
-        if (nb > 1) c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(X1[i * kMS + k], Y1[k * kMS + i], c1, 0, 0, 0);
-    }
-    __syncthreads();  // every operand read before any result is written (D may be an operand)
+        for (int a = 0; a < TILES; ++a)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        D0[(4 * v + q) * kMS + i] = c0[v];
-        if (nb > 1) D1[(4 * v + q) * kMS + i] = c1[v];
+            for (int b = 0; b < TILES; ++b) t[a][b] = mf64x4{0.0, 0.0, 0.0, 0.0};
     }
-    __syncthreads();
+};
+
+// D = X Y, X symmetric.
+template <int TILES>
+__device__ __forceinline__ RegMat<TILES> reg_mul(const RegMat<TILES>& X, const RegMat<TILES>& Y) {
+    RegMat<TILES> D;
+    D.zero();
+#pragma unroll
+    for (int c = 0; c < TILES; ++c)
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int a = 0; a < TILES; ++a)
+#pragma unroll
+                for (int b = 0; b < TILES; ++b)
+                    D.t[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(X.t[c][a][kk], Y.t[c][b][kk], D.t[a][b], 0, 0, 0);
+    // take the results out of the accumulators here: where a loop's branch lay
+    // between the last MFMA and the first read of its result, the compiled
+    // code waited too short (element 3 came back stale from the second
+    // squaring on); within one block the wait is right
+#pragma unroll
+    for (int a = 0; a < TILES; ++a)
+#pragma unroll
+        for (int b = 0; b < TILES; ++b)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                double x = D.t[a][b][kk];
+                asm volatile("" : "+v"(x));
+                D.t[a][b][kk] = x;
+            }
+    return D;
 }
 
-template <class R>
+template <class R, int TILES>
 __global__ __launch_bounds__(64) void k_precompute_mfma(R* __restrict__ Ptab, int M, int N, int Q, int FS,
                                                         double beta, double T, int nsteps, int scheme, double scale,
                                                         int keep_all, int pair) {
-    __shared__ double sm[6 * kMM];
-    __shared__ double spot[16];
+    constexpr int HM = 16 * TILES;  // padded block
+    constexpr int LS = HM + 1;      // LDS row stride
+    __shared__ double mat[2][HM * LS];
+    __shared__ double fac[2][3][HM];  // per block: 1/pivot, eliminated off-diagonal, Sherman-Morrison vector
+    __shared__ double spot[HM];
     const int l = threadIdx.x;
-    const int h = N / 2;
+    const int nblk = (N & 1) ? 1 : 2;
+    const int h = (N & 1) ? N : N / 2;
     int lx, ly;  // the class of this workgroup's slot
     table_slot_class(blockIdx.x, Q, N, lx, ly);
     const double two_pi = 6.283185307179586476925;
     const double sx = sin(two_pi * lx / M);
     const double sy = sin(two_pi * ly / M);
-    // per block b: base / product / scratch matrices, as offsets into sm
-    // (matrix b of a kind at sm + off + b * kMM)
-    int Bo = 0, Ro = 2 * kMM, To = 4 * kMM;
-    // the potential pot_j = M (cos e_j s_x + sin e_j s_y)^2, j < h, once per class
+    // the potential pot_j = M (cos e_j s_x + sin e_j s_y)^2, j < h
     if (l < h) {
         const double e = two_pi * l / N;
         const double a = cos(e) * sx + sin(e) * sy;
         spot[l] = (double)M * a * a;
     }
     __syncthreads();
-    auto pot = [&](int j) { return spot[j]; };
+    const int jl = l & 15, q = l >> 4;
+    // element (i, j) of tile (a, b), k-step kk, of this lane
+    auto row_of = [&](int a, int kk) { return 16 * a + 4 * kk + q; };
+    auto col_of = [&](int b) { return 16 * b + jl; };
     if (scheme == 0) {
         const double tau = T / nsteps;
         const double o = -0.5 * tau * beta;  // off-diagonal of I - tau A / 2
-        // lane l < 32: column c = l mod 16 of block b = l / 16
-        if (l < 32) {
-            const int b = l >> 4, c = l & 15;
-            double* Bb = sm + Bo + b * kMM;
-            if (c < h) {
-                const double cr = b == 0 ? o : -o;  // corners: periodic (p) / antiperiodic (q)
-                double d[16], cp[16], w[16], z[16];
-                for (int j = 0; j < h; ++j) d[j] = 1.0 + tau * beta + 0.5 * tau * pot(j);
-                const double g = -d[0];
-                // Thomas factorisation of Tm (d with d_0 - g, d_{h-1} - cr^2/g), solving
-                // Tm w = e_c and Tm z = u, u = (g, 0, .., 0, cr)
-                double prev_cp = 0.0, pw = 0.0, pz = 0.0;
-                for (int j = 0; j < h; ++j) {
-                    double tj = d[j];
-                    if (j == 0) tj -= g;
-                    if (j == h - 1) tj -= cr * cr / g;
-                    const double iden = 1.0 / (tj - (j ? o * prev_cp : 0.0));
-                    cp[j] = o * iden;
-                    w[j] = ((j == c ? 1.0 : 0.0) - (j ? o * pw : 0.0)) * iden;
-                    z[j] = ((j == 0 ? g : 0.0) + (j == h - 1 ? cr : 0.0) - (j ? o * pz : 0.0)) * iden;
-                    prev_cp = cp[j];
-                    pw = w[j];
-                    pz = z[j];
+        if (l < nblk) {
+            const double cr = l == 0 ? o : -o;  // corners: periodic (p) / antiperiodic (q)
+            // Thomas factorisation of Tm (d with d_0 - g, d_{h-1} - cr^2/g) and
+            // Tm z = u, u = (g, 0, .., 0, cr)
+            double* iden = fac[l][0];
+            double* cp = fac[l][1];
+            double* z = fac[l][2];
+            const double d0 = 1.0 + tau * beta + 0.5 * tau * spot[0];
+            const double g = -d0;
+            double pc = 0.0, pz = 0.0;
+            for (int j = 0; j < h; ++j) {
+                double tj = 1.0 + tau * beta + 0.5 * tau * spot[j];
+                double u = 0.0;
+                if (j == 0) {
+                    tj -= g;
+                    u += g;
                 }
-                for (int j = h - 2; j >= 0; --j) {
-                    w[j] -= cp[j] * w[j + 1];
-                    z[j] -= cp[j] * z[j + 1];
+                if (j == h - 1) {
+                    tj -= cr * cr / g;
+                    u += cr;
                 }
-                const double f = (w[0] + (cr / g) * w[h - 1]) / (1.0 + z[0] + (cr / g) * z[h - 1]);
-                for (int i = 0; i < 16; ++i) {
-                    const double inv = i < h ? w[i] - f * z[i] : 0.0;
-                    Bb[i * kMS + c] = i < h ? 2.0 * inv - (i == c ? 1.0 : 0.0) : 0.0;
-                }
-            } else {
-                for (int i = 0; i < 16; ++i) Bb[i * kMS + c] = i == c ? 1.0 : 0.0;
+                const double id = 1.0 / (tj - o * pc);
+                pc = o * id;
+                pz = (u - o * pz) * id;
+                iden[j] = id;
+                cp[j] = pc;
+                z[j] = pz;
             }
-        }
-        for (int e = l; e < 2 * 256; e += 64) {
-            const int b = e >> 8, i = (e >> 4) & 15, j = e & 15;
-            sm[Ro + b * kMM + i * kMS + j] = i == j ? 1.0 : 0.0;
+            for (int j = h - 2; j >= 0; --j) {
+                pz = z[j] - cp[j] * pz;
+                z[j] = pz;
+            }
         }
         __syncthreads();
-        // binary powering: R = C^n (the roles of the three matrices rotate)
-        int n = nsteps;
-        while (n > 0) {
-            if (n & 1) {
-                mm16_pair(sm + Ro, sm + Bo, sm + To, sm + Ro + kMM, sm + Bo + kMM, sm + To + kMM, 2, l);
-                const int t = Ro;
-                Ro = To;
-                To = t;
+        const int b = TILES == 1 ? (l >> 4) & 1 : l >> 5;
+        const int c = TILES == 1 ? l & 15 : l & 31;
+        if (l < 2 * HM && b < nblk && c < h) {
+            const double cr = b == 0 ? o : -o;
+            const double g = -(1.0 + tau * beta + 0.5 * tau * spot[0]);
+            const double* iden = fac[b][0];
+            const double* cp = fac[b][1];
+            const double* z = fac[b][2];
+            double* w = mat[b] + c;
+            double p = 0.0;
+            for (int j = 0; j < h; ++j) {
+                p = ((j == c ? 1.0 : 0.0) - o * p) * iden[j];
+                w[j * LS] = p;
             }
-            n >>= 1;
-            if (n) {
-                mm16_pair(sm + Bo, sm + Bo, sm + To, sm + Bo + kMM, sm + Bo + kMM, sm + To + kMM, 2, l);
-                const int t = Bo;
-                Bo = To;
-                To = t;
+            const double wl = p;
+            for (int j = h - 2; j >= 0; --j) {
+                p = w[j * LS] - cp[j] * p;
+                w[j * LS] = p;
             }
+            const double f = (p + (cr / g) * wl) / (1.0 + z[0] + (cr / g) * z[h - 1]);
+            for (int j = 0; j < h; ++j) w[j * LS] = 2.0 * (w[j * LS] - f * z[j]) - (j == c ? 1.0 : 0.0);
         }
-    } else {
-        // X = T A / 2^s with ||T A||_inf / 2^s <= 1/2 (the larger of the two blocks' norms)
+        __syncthreads();
+    }
+    // X = T A / 2^sq with ||X||_inf <= 1/2 (the larger of the blocks' norms; EXACT)
+    int sq = 0;
+    double xs = 0.0;
+    if (scheme != 0) {
         double nrm = 0.0;
         for (int i = 0; i < h; ++i)  // row sums: |diagonal| plus at most 2 beta off the diagonal
-            nrm = fmax(nrm, fabs(-2.0 * beta - pot(i)) + 2.0 * beta);
+            nrm = fmax(nrm, fabs(-2.0 * beta - spot[i]) + 2.0 * beta);
         nrm *= T;
-        int sq = 0;
         while (nrm > 0.5) {
             nrm *= 0.5;
             ++sq;
         }
-        const double xs = T * ldexp(1.0, -sq);
-        for (int e = l; e < 2 * 256; e += 64) {
-            const int b = e >> 8, i = (e >> 4) & 15, j = e & 15;
-            double v = 0.0;
-            if (i < h && j < h) {
-                const double wrap = b == 0 ? 1.0 : -1.0;
-                if (i == j) v = -2.0 * beta - pot(i);
-                if (j == (i + 1) % h) v += (i + 1 < h) ? beta : wrap * beta;
-                if (j == (i + h - 1) % h) v += (i >= 1) ? beta : wrap * beta;
-            }
-            sm[Bo + b * kMM + i * kMS + j] = v * xs;
-            sm[Ro + b * kMM + i * kMS + j] = i == j ? 1.0 : 0.0;
-        }
-        __syncthreads();
-        // Horner: E = I + X (I + X/2 (I + X/3 (... (I + X/16))))
-        for (int k = 16; k >= 1; --k) {
-            mm16_pair(sm + Bo, sm + Ro, sm + To, sm + Bo + kMM, sm + Ro + kMM, sm + To + kMM, 2, l);
-            for (int e = l; e < 2 * 256; e += 64) {
-                const int b = e >> 8, i = (e >> 4) & 15, j = e & 15;
-                sm[Ro + b * kMM + i * kMS + j] = (i == j ? 1.0 : 0.0) + sm[To + b * kMM + i * kMS + j] / k;
-            }
-            __syncthreads();
-        }
-        for (int s2 = 0; s2 < sq; ++s2) {
-            mm16_pair(sm + Ro, sm + Ro, sm + To, sm + Ro + kMM, sm + Ro + kMM, sm + To + kMM, 2, l);
-            const int t = Ro;
-            Ro = To;
-            To = t;
-        }
+        xs = T * ldexp(1.0, -sq);
     }
-    // packed upper triangles of both blocks, symmetrised, scaled, stored as R
+    for (int blk = 0; blk < nblk; ++blk) {
+        RegMat<TILES> X, P;
+        const double wrap = blk == 0 ? 1.0 : -1.0;
+#pragma unroll
+        for (int a = 0; a < TILES; ++a)
+#pragma unroll
+            for (int b = 0; b < TILES; ++b)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) {
+                    const int i = row_of(a, kk), j = col_of(b);
+                    double v = 0.0;
+                    if (i < h && j < h) {
+                        if (scheme == 0) {
+                            v = mat[blk][i * LS + j];
+                        } else {
+                            if (i == j) v = -2.0 * beta - spot[i];
+                            if (j == (i + 1 < h ? i + 1 : 0)) v += (i + 1 < h) ? beta : wrap * beta;
+                            if (j == (i >= 1 ? i - 1 : h - 1)) v += (i >= 1) ? beta : wrap * beta;
+                            v *= xs;
+                        }
+                    }
+                    X.t[a][b][kk] = v;
+                }
+        if (scheme == 0) {
+            // binary powering from the lowest set bit of n on
+            int n = nsteps;
+            while ((n & 1) == 0) {
+                X = reg_mul<TILES>(X, X);
+                n >>= 1;
+            }
+            P = X;
+            for (n >>= 1; n > 0; n >>= 1) {
+                X = reg_mul<TILES>(X, X);
+                if (n & 1) P = reg_mul<TILES>(X, P);
+            }
+        } else {
+            auto plus_identity = [&](RegMat<TILES>& E, double s) {
+#pragma unroll
+                for (int a = 0; a < TILES; ++a)
+#pragma unroll
+                    for (int b = 0; b < TILES; ++b)
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk)
+                            E.t[a][b][kk] = s * E.t[a][b][kk] + (row_of(a, kk) == col_of(b) ? 1.0 : 0.0);
+            };
+            // Horner: E = I + X (I + X/2 (I + X/3 (... (I + X/16))))
+            P = X;
+            plus_identity(P, 1.0 / 16.0);
+            for (int k = 15; k >= 1; --k) {
+                P = reg_mul<TILES>(X, P);
+                plus_identity(P, 1.0 / k);
+            }
+            for (int s2 = 0; s2 < sq; ++s2) P = reg_mul<TILES>(P, P);
+        }
+#pragma unroll
+        for (int a = 0; a < TILES; ++a)
+#pragma unroll
+            for (int b = 0; b < TILES; ++b)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) mat[blk][row_of(a, kk) * LS + col_of(b)] = P.t[a][b][kk];
+    }
+    __syncthreads();
+    // packed upper triangles of the blocks, symmetrised, scaled, stored as R
     const int Eh = h * (h + 1) / 2;
     const int CS = table_class_stride(N, (int)sizeof(R));
     R* dst = Ptab + (size_t)blockIdx.x * CS;
+    const float inv_h = 1.0f / (float)h;
     double pmax = 0.0;
-    for (int e = l; e < 2 * h * h; e += 64) {
-        const int b = e / (h * h), r = e - b * h * h, i = r / h, j = r - (r / h) * h;
-        if (j >= i) {
-            const double* Rb = sm + Ro + b * kMM;
-            const double u = 0.5 * (Rb[i * kMS + j] + Rb[j * kMS + i]);
-            pmax = fmax(pmax, fabs(u));
-            if (!pair) dst[b * Eh + i * h - i * (i - 1) / 2 + (j - i)] = (R)(u * scale);
+    for (int b = 0; b < nblk; ++b) {
+        auto at = [&](int i, int j) { return 0.5 * (mat[b][i * LS + j] + mat[b][j * LS + i]); };
+        for (int e = l; e < h * h; e += 64) {
+            const int i = fdiv(e, inv_h), j = e - i * h;
+            if (j >= i) {
+                const double u = at(i, j);
+                pmax = fmax(pmax, fabs(u));
+                if (!pair) dst[b * Eh + i * h - i * (i - 1) / 2 + (j - i)] = (R)(u * scale);
+            }
         }
-    }
-    if (pair) {
-        for (int b = 0; b < 2; ++b) {
-            const double* Rb = sm + Ro + b * kMM;
-            store_pair_block<R>(Ptab, M, N, b, lx, ly, h, scale, l,
-                                [&](int i, int j) { return 0.5 * (Rb[i * kMS + j] + Rb[j * kMS + i]); });
-        }
+        if (pair) store_pair_block<R>(Ptab, M, N, b, lx, ly, h, scale, l, at);
     }
     for (int off = 32; off >= 1; off >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, off, 64));
     store_class_flags<R>(Ptab, M, N, Q, FS, lx, ly, !keep_all && pmax < (sizeof(R) == 4 ? 0x1p-30 : 0x1p-60), l, pair);
     if (!pair)
-        for (int e = 2 * Eh + l; e < CS; e += 64) dst[e] = R(0);
+        for (int e = nblk * Eh + l; e < CS; e += 64) dst[e] = R(0);
 }
 
 // ---------------------------------------------------------------------------
@@ -888,12 +949,15 @@ hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int n
     const size_t lds = (size_t)(4 * h * h + h) * sizeof(double);
     // the inverse FFT's 1/M^2, and for even N the 1/2 of the p/q recombination
     const double scale = ((N & 1) ? 1.0 : 0.5) / ((double)M * (double)M);
-    // matrix cores for blocks of 9..16 (N = 18..32, the padded 16 x 16 products
-    // pay off there: N = 32 at 2048^2, 400 steps: 8.6 -> 2 ms; N = 16 is
-    // faster on the scalar path); SE2N_SCALAR_PRECOMPUTE forces the scalar one
-    if (!(N & 1) && h > 8 && h <= 16 && std::getenv("SE2N_SCALAR_PRECOMPUTE") == nullptr) {
-        hipLaunchKernelGGL((k_precompute_mfma<R>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
-                           flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
+    // matrix cores for blocks of at most 32; SE2N_SCALAR_PRECOMPUTE forces the
+    // scalar build, which odd N above 32 keeps
+    if (h <= 32 && std::getenv("SE2N_SCALAR_PRECOMPUTE") == nullptr) {
+        if (h <= 16)
+            hipLaunchKernelGGL((k_precompute_mfma<R, 1>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
+                               flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
+        else
+            hipLaunchKernelGGL((k_precompute_mfma<R, 2>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
+                               flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_precompute<R>), dim3((unsigned)slots), dim3(64), lds, st, Ptab, M, N, Q,

@@ -504,20 +504,18 @@ const void* find_propagators(se2n_plan p, double T, double beta, int n_steps, se
 
 // Estimated milliseconds of the two CN schedules on MI355X, from measured
 // per-unit costs: the iterated kernel per mode and step, the FP64 propagator
-// build per class (it grows with (N/2)^3 and with the binary powering's
-// log2 n products).  Used only to choose a schedule for an uncached key.
-// (FP32, 2048^2, N = 32: 6.66 ms for 400 iterated steps; the 400-step table
-// takes 2.6 ms on the matrix cores (blocks of 9..16), 8.6 ms on the scalar
-// path, whose cost grows with (N/2)^3.)
+// build per class (on the matrix cores, one 16 x 16 tile or four per block)
+// and per product of the binary powering.  Used only to choose a schedule
+// for an uncached key.
+// (FP32: 2048^2, N = 32, 6.66 ms for 400 iterated steps; builds of 1024^2, N = 32,
+// 200 steps 0.22 ms and of 384^2, N = 64, 100 steps 0.18 ms.)
 double est_iterated_ms(int M, int N, int n) {
     return 8.0e-9 * (double)(M / 2 + 1) * M * n * (N / 32.0);
 }
 double est_precompute_ms(int M, int N, int n) {
-    const double h = N / 2.0;
     const double classes = (double)table_slots(M, N);  // one build per stored class
     const double products = (std::log2((double)n) + 3.0) / 11.6;
-    if (h > 8 && h <= 16) return 1.0e-5 * classes * products;
-    return 3.3e-5 * classes * (h * h * h / 4096.0) * products;
+    return (N <= 32 ? 7.0e-6 : 4.5e-5) * classes * products;
 }
 
 // Whether this CN diffusion runs the iterated schedule.  AUTO: a cached
