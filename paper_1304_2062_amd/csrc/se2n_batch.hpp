@@ -8,6 +8,7 @@
 
 #include "se2n_fft.hpp"
 #include "se2n_internal.hpp"
+#include "se2n_pair.hpp"
 
 namespace se2n {
 
@@ -29,6 +30,10 @@ struct BItem {
     int imask;  // 1: the inverse column pass takes negligible modes as zero, and the solve stores none
     float ocoef, oscale;  // orientation: -2 pi^2 sigma^2 / M^2 and sqrt(M)/M^2
     FftPlan planH, planM;
+    // items on the pair path (batch_pair): layout of spec, rows of an inverse
+    // row tile and pairs per round
+    PairLay lay;
+    int inv_rows, inv_G;
 };
 
 // Passes of a batch, in launch order.
@@ -45,6 +50,11 @@ enum BatchKind {
     BK_ROW_INV_MEAN,
     BK_DECODE,
     BK_ORIENT_STENCIL,  // one launch per (M, sigma): `cls` is the radius, the taps are arguments
+    // the pair path: forward rows, middle, inverse rows (maximum, mean)
+    BK_PAIR_FWD,
+    BK_PAIR_MID,
+    BK_PAIR_MAX,
+    BK_PAIR_MEAN,
     BK_COUNT
 };
 
@@ -77,6 +87,15 @@ template <int MS>
 constexpr bool kBatchBlocked = MS == 512 || MS == 768 || MS == 1024;
 inline bool batch_blocked(int M) { return M == 512 || M == 768 || M == 1024; }
 static_assert(512 % kRowBlk == 0 && 768 % kRowBlk == 0 && 1024 % kRowBlk == 0, "row blocks of the blocked sides");
+
+// Items that run their three passes on the pair path (se2n_pair.hpp): compiled
+// sides whose columns fit.  The other sides keep the five separate passes: the
+// batched pair kernels are compiled per side.
+inline bool batch_pair(int M, int N) { return batch_class(M) != 0 && pair_fits(M, N, 4); }
+
+// One pass of the pair path over the tiles of images of side M (se2n_batch_pair.hip).
+hipError_t launch_batch_pair(int kind, int M, int ept, bool walk, int threads, const BItem* items, const int4* tiles,
+                             int ntiles, int grid, size_t lds, hipStream_t st);
 
 // Launch one pass (size class `cls`, solve instance N): `grid` workgroups
 // walk tiles[0..ntiles) with stride grid.

@@ -33,6 +33,12 @@ namespace {
 constexpr int kMaxItems = 4096;
 constexpr int kMaxPlansPerDevice = 4;
 constexpr int kPixelsPerTile = 8192;  // clear / decode tiles
+// The pair path's groups and branches (build_schedule), measured on 64 images
+// of 128^2..1024^2 and on 30 of 64^2..512^2: one branch 3.51 and 0.84 ms, two
+// 3.16 and 0.69, three 3.20 and 0.66, four 3.22 and 0.85; groups of 32, 64, 128
+// and 256 MB on two branches 3.18, 3.16, 3.17, 3.23 ms.
+constexpr int kPairBranches = 2;
+constexpr size_t kPairGroupBytes = (size_t)64 << 20;
 
 // The pointer-free description of an item: what a batch plan is built for.
 struct Shape {
@@ -364,8 +370,43 @@ struct TableKey {
     }
 };
 
+// Tiles of a pass of the pair path (kinds BK_PAIR_*) over the items `which`,
+// image after image.  A column's tiles lie so that each XCD (the
+// launch's workgroups go to the 8 XCDs in turn) gets neighbouring columns:
+// an item's M tiles are a multiple of 8.
+std::vector<int4> pair_tiles(const std::vector<Shape>& sh, const std::vector<PairGeom>& geom,
+                             const std::vector<int>& which, int kind) {
+    std::vector<int4> out;
+    for (int i : which) {
+        const Shape& x = sh[i];
+        const PairGeom& g = geom[i];
+        const int np = pair_count(x.N);
+        if (kind == BK_PAIR_FWD) {
+            for (int t0 = 0; t0 < np; t0 += g.fwd_pairs) {
+                const int t1 = std::min(np, t0 + g.fwd_pairs), nrb = x.M / g.fwd_rows;
+                for (int w = 0; w < nrb; ++w)
+                    out.push_back(make_int4(i, xcd_contiguous(w, nrb), t0, t1));
+            }
+        } else if (kind == BK_PAIR_MID) {
+            const int n = x.M / 2 * pair_nblk(x.N);
+            for (int w = 0; w < n; ++w) {
+                int kx, blk;
+                pair_mid_col(w, x.M / 2, pair_nblk(x.N), kx, blk);
+                out.push_back(make_int4(i, kx, blk, 0));
+            }
+        } else {
+            if ((kind == BK_PAIR_MAX) != (x.proj == SE2N_PROJ_MAX)) continue;
+            const int nrb = x.M / g.inv_rows;
+            for (int w = 0; w < nrb; ++w)
+                out.push_back(make_int4(i, xcd_contiguous(w, nrb), 0, np));
+        }
+    }
+    return out;
+}
+
 struct Launch {
     int kind, N, cls;
+    int ept, threads, walk, branch;  // pair path (branch -1: the stem of the graph)
     const char* name;
     int ntiles, grid;
     size_t lds;
@@ -388,6 +429,10 @@ const char* kind_name(int kind, int N) {
         case BK_ROW_INV_MEAN: return "b_row_inv_mean";
         case BK_DECODE: return "b_decode_max";
         case BK_ORIENT_STENCIL: return "b_orient_stencil";
+        case BK_PAIR_FWD: return "b_lift_row_fwd";
+        case BK_PAIR_MID: return "b_col_solve";
+        case BK_PAIR_MAX: return "b_row_inv_max";
+        case BK_PAIR_MEAN: return "b_row_inv_mean";
         case BK_SOLVE:
             if (N >= 4 && N <= 64 && N % 2 == 0) {
                 const int k = N / 2;
@@ -407,6 +452,7 @@ struct BatchPlan {
     std::string sig;
     uint64_t hash = 0;
     std::vector<Shape> shapes;
+    std::vector<PairGeom> geom;  // of the items on the pair path
     se2n_tune tune = kDefaultTune;
     Layout layout;
     int num_cu = 0;
@@ -462,6 +508,14 @@ bool g_prof_on = false;
 std::vector<ProfRec> g_prof_pending;
 std::map<std::string, std::pair<int, double>> g_prof_acc;
 
+hipError_t launch_one(const BatchPlan& bp, const Launch& L, hipStream_t st) {
+    const int4* tiles = bp.d_tiles + L.tile_off;
+    if (L.threads)
+        return launch_batch_pair(L.kind, L.cls, L.ept, L.walk != 0, L.threads, bp.d_items, tiles, L.ntiles, L.grid, L.lds,
+                                 st);
+    return launch_batch(L.kind, L.N, L.cls, bp.d_items, tiles, L.ntiles, L.grid, L.lds, st, &L.taps);
+}
+
 int build_schedule(BatchPlan& bp) {
     bp.drop_schedule();
     // tile lists per launch: pass x size class (x N for the solve, x projection for the inverse rows)
@@ -469,10 +523,16 @@ int build_schedule(BatchPlan& bp) {
         int kind, N, cls;
         std::vector<int4> tiles;
         OrientTaps taps;
+        int ept = 0, threads = 0, walk = 0, branch = -1;
+        size_t lds = 0;
     };
     std::vector<Part> parts;
     auto add_pass_fwd = [&](int kind, int pass) {
         std::vector<int4> all = ordered_tiles(bp.shapes, bp.tune, pass);
+        if (pass >= 3 && pass <= 8)  // the items on the pair path have their own passes
+            all.erase(std::remove_if(all.begin(), all.end(),
+                                     [&](const int4& t) { return batch_pair(bp.shapes[t.x].M, bp.shapes[t.x].N); }),
+                      all.end());
         if (kind == BK_ORIENT_STENCIL) {
             // one launch per (M, sigma), largest sides first
             std::vector<std::pair<int, double>> keys;
@@ -538,10 +598,65 @@ int build_schedule(BatchPlan& bp) {
             for (size_t k = first; k < parts.size(); ++k) std::reverse(parts[k].tiles.begin(), parts[k].tiles.end());
         }
     };
+    // The pair path: images of one side and N form groups of at most
+    // kPairGroupBytes of spectrum, and each group runs its passes back to back
+    // (forward rows, middle, inverse rows), so that a pass finds the pass
+    // before in the memory-side cache.  The groups go to kPairBranches
+    // branches of the graph, the largest first to the least loaded one:
+    // launches of different groups overlap, where one's last workgroups leave
+    // compute units, LDS or bandwidth idle.
+    auto add_pair = [&]() {
+        std::map<std::pair<int, int>, std::vector<std::vector<int>>> sets;  // (M, N) -> groups
+        std::map<std::pair<int, int>, size_t> fill;
+        for (int i = 0; i < (int)bp.shapes.size(); ++i) {
+            const Shape& x = bp.shapes[i];
+            if (!batch_pair(x.M, x.N)) continue;
+            const size_t bytes = (size_t)x.N * x.M * (x.M / 2) * sizeof(C2<float>);
+            auto& v = sets[{x.M, x.N}];
+            size_t& f = fill[{x.M, x.N}];
+            if (v.empty() || f + bytes > kPairGroupBytes) {
+                v.emplace_back();
+                f = 0;
+            }
+            v.back().push_back(i);
+            f += bytes;
+        }
+        std::vector<std::pair<double, std::vector<int>>> groups;
+        for (auto& kv : sets)
+            for (auto& v : kv.second)
+                groups.emplace_back((double)v.size() * kv.first.first * kv.first.first * kv.first.second, v);
+        std::stable_sort(groups.begin(), groups.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+        double load[kPairBranches] = {};
+        for (const auto& gr : groups) {
+            const int br = (int)(std::min_element(load, load + kPairBranches) - load);
+            load[br] += gr.first;
+            const Shape& x = bp.shapes[gr.second[0]];
+            const PairGeom& g = bp.geom[gr.second[0]];
+            const int M = x.M, np = pair_count(x.N);
+            auto part = [&](int kind, int ept, int threads, int walk, size_t lds) {
+                Part p{kind, 0, M, pair_tiles(bp.shapes, bp.geom, gr.second, kind), {}};
+                if (p.tiles.empty()) return;
+                p.ept = ept;
+                p.threads = threads;
+                p.walk = walk;
+                p.lds = lds;
+                p.branch = br;
+                parts.push_back(std::move(p));
+            };
+            part(BK_PAIR_FWD, g.fwd_ept, g.fwd_threads, 0, pair_lds_bytes(M, g.fwd_rows, 4));
+            part(BK_PAIR_MID, g.mid_ept, g.mid_threads, g.mid_grid < M / 2 * pair_nblk(x.N),
+                 pair_lds_bytes(M, pair_hs(x.N), 4));
+            const size_t lds = pair_lds_bytes(M, g.inv_rows * g.inv_G, 4) +
+                               (g.inv_G < np ? (size_t)g.inv_rows * M * sizeof(float) : 0);
+            part(BK_PAIR_MAX, g.inv_ept, g.inv_threads, 0, lds);
+            part(BK_PAIR_MEAN, g.inv_ept, g.inv_threads, 0, lds);
+        }
+    };
     add_pass(BK_ORIENT_STENCIL, 9);
     add_pass(BK_ORIENT_ROW, 0);
     add_pass(BK_ORIENT_COL, 1);
     add_pass(BK_ORIENT_INV, 2);
+    add_pair();
     add_pass(BK_LIFT_ROW, 3);
     add_pass(BK_COL_FWD, 4, true);
     add_pass(BK_SOLVE, 5);
@@ -563,9 +678,14 @@ int build_schedule(BatchPlan& bp) {
         L.ntiles = (int)p.tiles.size();
         L.tile_off = flat.size();
         L.taps = p.taps;
+        L.ept = p.ept;
+        L.threads = p.threads;
+        L.walk = p.walk;
+        L.branch = p.branch;
         // LDS: the largest need of the part's images
-        size_t lds = 0;
+        size_t lds = p.lds;
         for (const int4& t : p.tiles) {
+            if (p.threads) break;  // pair path: one tile shape per launch
             const Shape& x = bp.shapes[t.x];
             const int M = x.M, H = M / 2;
             const GeomCore g = geom_core<float>(M);
@@ -604,7 +724,12 @@ int build_schedule(BatchPlan& bp) {
         if (lds > 160 * 1024) return fail(SE2N_EUNSUPPORTED, "batched pass %s needs %zu bytes of LDS", L.name, lds);
         L.lds = lds;
         int grid = L.ntiles;
-        if (bp.tune.wg_per_cu > 0) {
+        if (L.threads) {
+            // pair path: a workgroup per tile whatever the tune says (two
+            // resident walkers per unit: 64 images of 128^2..1024^2 3.58
+            // against 3.49 ms), or the middle pass's walkers
+            if (L.walk) grid = std::min(L.ntiles, bp.num_cu);
+        } else if (bp.tune.wg_per_cu > 0) {
             int occ = 0;
             SE2N_HIP(batch_occupancy(L.kind, L.N, L.cls, lds, &occ), "occupancy query of a batched kernel");
             if (occ < 1) return fail(SE2N_EUNSUPPORTED, "batched pass %s cannot be resident", L.name);
@@ -621,13 +746,47 @@ int build_schedule(BatchPlan& bp) {
     SE2N_HIP(hipMemcpy(bp.d_tiles, flat.data(), flat.size() * sizeof(int4), hipMemcpyHostToDevice),
              "upload of batch tiles");
 
-    // capture the launches into a graph (kernel nodes only)
+    // capture the launches into a graph (kernel nodes only): the stem (the
+    // orientation passes) first, then the branches of the pair path beside the
+    // other items' passes, joined at the end
+    struct Fork {
+        hipStream_t st[kPairBranches] = {};
+        hipEvent_t at = nullptr, done[kPairBranches] = {};
+        bool used[kPairBranches] = {};
+        ~Fork() {
+            for (int k = 0; k < kPairBranches; ++k) {
+                if (st[k]) (void)hipStreamDestroy(st[k]);
+                if (done[k]) (void)hipEventDestroy(done[k]);
+            }
+            if (at) (void)hipEventDestroy(at);
+        }
+    } fork;
+    for (int k = 0; k < kPairBranches; ++k) {
+        SE2N_HIP(hipStreamCreateWithFlags(&fork.st[k], hipStreamNonBlocking), "branch capture stream");
+        SE2N_HIP(hipEventCreateWithFlags(&fork.done[k], hipEventDisableTiming), "branch event");
+    }
+    SE2N_HIP(hipEventCreateWithFlags(&fork.at, hipEventDisableTiming), "fork event");
     SE2N_HIP(hipStreamBeginCapture(bp.cap, hipStreamCaptureModeRelaxed), "begin graph capture");
     hipError_t le = hipSuccess;
+    bool forked = false;
     for (const Launch& L : bp.launches) {
-        le = launch_batch(L.kind, L.N, L.cls, bp.d_items, bp.d_tiles + L.tile_off, L.ntiles, L.grid, L.lds, bp.cap,
-                          &L.taps);
+        hipStream_t to = bp.cap;
+        if (L.branch >= 0) {
+            if (!forked) le = hipEventRecord(fork.at, bp.cap);
+            forked = true;
+            to = fork.st[L.branch];
+            if (le == hipSuccess && !fork.used[L.branch]) le = hipStreamWaitEvent(to, fork.at, 0);
+            fork.used[L.branch] = true;
+        }
+        if (le == hipSuccess) le = launch_one(bp, L, to);
         if (le != hipSuccess) break;
+    }
+    for (int k = 0; k < kPairBranches; ++k) {
+        if (!fork.used[k]) continue;
+        // every branch joins, also after a failed launch, so that the capture can end
+        const hipError_t a = hipEventRecord(fork.done[k], fork.st[k]);
+        const hipError_t b = a == hipSuccess ? hipStreamWaitEvent(bp.cap, fork.done[k], 0) : a;
+        if (le == hipSuccess) le = b;
     }
     hipGraph_t g = nullptr;
     const hipError_t ee = hipStreamEndCapture(bp.cap, &g);
@@ -664,6 +823,7 @@ int build_plan(BatchPlan& bp, const se2n_item* items, int count, hipStream_t st)
     }
 
     bp.items.assign(count, BItem{});
+    bp.geom.assign(count, PairGeom{});
     for (int i = 0; i < count; ++i) {
         const Shape& x = bp.shapes[i];
         const int M = x.M;
@@ -680,10 +840,11 @@ int build_plan(BatchPlan& bp, const se2n_item* items, int count, hipStream_t st)
         const TableKey tk{M, x.N, x.n, x.scheme, x.T, x.beta};
         if (!bp.tables.count(tk)) {
             void* d = nullptr;
-            const hipError_t e = dev_malloc(&d, table_bytes(M, x.N, 4));  // class-major propagators + class flags
+            const bool pair = batch_pair(M, x.N);
+            const hipError_t e = dev_malloc(&d, pair ? pair_table_bytes(M, x.N, 4) : table_bytes(M, x.N, 4));
             if (e != hipSuccess) return fail(SE2N_ENOMEM, "hipMalloc of a propagator table: %s", hipGetErrorString(e));
             bp.tables[tk] = d;
-            SE2N_HIP(launch_precompute<float>((float*)d, M, x.N, x.beta, x.T, x.n, x.scheme, st),
+            SE2N_HIP(launch_precompute<float>((float*)d, M, x.N, x.beta, x.T, x.n, x.scheme, st, false, pair),
                      "propagator precompute launch");
         }
         const GeomCore g = geom_core<float>(M);
@@ -709,6 +870,12 @@ int build_plan(BatchPlan& bp, const se2n_item* items, int count, hipStream_t st)
         b.oscale = (float)(std::sqrt((double)M) / ((double)M * M));
         b.planH = make_fft_plan(M / 2, M);
         b.planM = make_fft_plan(M, M);
+        if (batch_pair(M, x.N)) {
+            bp.geom[i] = pair_geom(M, x.N, 4, bp.num_cu);
+            b.lay = bp.geom[i].lay;
+            b.inv_rows = bp.geom[i].inv_rows;
+            b.inv_G = bp.geom[i].inv_G;
+        }
         // the invariants the batched bodies rely on (512 threads, 8 elements each)
         const int H = M / 2;
         if (g.rows * H > 8 * kBatchThreads || g.cols * M > 8 * kBatchThreads ||
@@ -769,9 +936,7 @@ int run_plan(BatchPlan& bp, const se2n_item* items, void* ws, hipStream_t st) {
     for (const Launch& L : bp.launches) {
         hipEvent_t a = new_event(), b = new_event();
         if (a) (void)hipEventRecord(a, st);
-        const hipError_t e =
-            launch_batch(L.kind, L.N, L.cls, bp.d_items, bp.d_tiles + L.tile_off, L.ntiles, L.grid, L.lds, st,
-                         &L.taps);
+        const hipError_t e = launch_one(bp, L, st);
         if (b) (void)hipEventRecord(b, st);
         if (a && b) g_prof_pending.push_back({L.name, a, b});
         if (e != hipSuccess) return hip_fail(e, "batched kernel launch");

@@ -104,3 +104,34 @@ def test_restoration_on_the_pair_path(monkeypatch, M, N, dtype, dynamic):
     assert float(want.abs().max()) < 2.0
     assert torch.equal(join, join5)
     assert _rel(got, want) < (2e-5 if dtype == torch.float32 else 1e-10)
+
+
+@pytest.mark.parametrize("shapes", [[(128, 4), (128, 64)], [(1024, 34), (1024, 32), (64, 16)], [(768, 40), (192, 6)],
+                                    [(512, 32)] * 5 + [(256, 30), (384, 48)]])
+def test_batch_on_the_pair_path(shapes):
+    """Batched items against the single-image path: the smallest and largest
+    blocks of a side, groups of several images and of one, both projections,
+    beside items that keep the five passes (1024, N = 34 and sides without a
+    compiled body), replayed with other work between."""
+    from paper_1304_2062_amd import se2n
+    items, want = [], []
+    for i, (M, N) in enumerate(shapes):
+        f, mask = _image(M, 100 + i, torch.float32)
+        proj = "mean" if i % 3 == 1 else "max"
+        items.append(se2n.BatchItem(f, mask, N, 1.0, 1.0, 50, proj=proj))
+        plan = se2n.Plan(M, N, torch.float32)
+        want.append(plan.inpaint(f, mask, 1.0, 1.0, 50, proj=proj))
+        torch.cuda.synchronize()
+        plan.close()
+    ws = se2n.batch_workspace(items)
+    ws.fill_(255)
+    for replay in range(3):
+        print(f"pair batch {shapes} replay {replay}", flush=True)
+        for it in items:
+            it.out.fill_(float("nan"))
+        out = se2n.inpaint_batched(items, ws)
+        for got, it, (ref, rmap) in zip(out, items, want):
+            assert torch.equal(it.rmap_out, rmap)
+            assert _rel(got, ref) < TOL[torch.float32]
+        (torch.randn(1 << 20, device="cuda") * 2).sum().item()
+    se2n.batch_clear()
