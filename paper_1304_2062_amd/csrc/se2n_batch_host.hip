@@ -841,7 +841,7 @@ int build_plan(BatchPlan& bp, const se2n_item* items, int count, hipStream_t st)
         if (!bp.tables.count(tk)) {
             void* d = nullptr;
             const bool pair = batch_pair(M, x.N);
-            const hipError_t e = dev_malloc(&d, pair ? pair_table_bytes(M, x.N, 4) : table_bytes(M, x.N, 4));
+            const hipError_t e = dev_malloc(&d, pair ? pair_table_bytes(M, x.N, 4, false) : table_bytes(M, x.N, 4));
             if (e != hipSuccess) return fail(SE2N_ENOMEM, "hipMalloc of a propagator table: %s", hipGetErrorString(e));
             bp.tables[tk] = d;
             SE2N_HIP(launch_precompute<float>((float*)d, M, x.N, x.beta, x.T, x.n, x.scheme, st, false, pair),

@@ -333,10 +333,11 @@ hipError_t launch_orient_stencil(const float* f, const uint8_t* mask, uint8_t* r
 
 // keep_all: flag no class as negligible (every mode is then read, propagated
 // and stored; used to time the passes without the skip).
-// pair: the element-major table of the pair path (pair_table_bytes).
+// pair: 1 the element-major table of the pair path (pair_table_bytes), 2 the
+// one of halved columns.
 template <class R>
 hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int nsteps, int scheme,
-                             hipStream_t st, bool keep_all = false, bool pair = false);
+                             hipStream_t st, bool keep_all = false, int pair = 0);
 
 // Per-mode Crank-Nicolson integrated step by step (se2n_solve_iter.hip):
 // n_steps steps of T / n_steps on every mode of the half spectrum, in place,

@@ -230,7 +230,7 @@ template <class R>
 __device__ void store_class_flags(R* Ptab, int M, int N, int Q, int FS, int lx, int ly, bool negligible, int tid,
                                   int pair) {
     uint8_t* flags = reinterpret_cast<uint8_t*>(
-        Ptab + (pair ? pair_table_entries(M, N) : table_slots(M, N) * (size_t)table_class_stride(N, (int)sizeof(R))));
+        Ptab + (pair ? pair_table_entries(M, N, pair == 2) : table_slots(M, N) * (size_t)table_class_stride(N, (int)sizeof(R))));
     if (tid == 0) {
         flags[(size_t)lx * FS + ly] = negligible ? 1 : 0;
         if (table_sym(N)) flags[(size_t)ly * FS + lx] = negligible ? 1 : 0;
@@ -244,12 +244,13 @@ __device__ void store_class_flags(R* Ptab, int M, int N, int Q, int FS, int lx, 
 // reflection r -> N/4 - r (an index that wraps around turns the sign of an
 // antiperiodic slice).  at(i, j) is the symmetrised entry of this class.
 template <class R, class F>
-__device__ void store_pair_block(R* Ptab, int M, int N, int b, int lx, int ly, int h, double scale, int tid, F&& at) {
+__device__ void store_pair_block(R* Ptab, int M, int N, int halved, int b, int lx, int ly, int h, double scale, int tid,
+                                 F&& at) {
     const int Eh = h * (h + 1) / 2;
-    const int QP = pair_qp(M);
+    const int QP = pair_qp(M, halved);
     const int nblk = pair_nblk(N);
-    R* d0 = Ptab + ((size_t)(lx * nblk + b) * Eh) * QP + ly;
-    R* d1 = Ptab + ((size_t)(ly * nblk + b) * Eh) * QP + lx;
+    R* d0 = Ptab + ((size_t)(lx * nblk + b) * Eh) * QP + pair_class_pos(M, halved, ly);
+    R* d1 = Ptab + ((size_t)(ly * nblk + b) * Eh) * QP + pair_class_pos(M, halved, lx);
     const bool both = table_sym(N) && lx != ly;
     const int g = N / 4;
     const float inv_h = 1.0f / (float)h;
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(64) void k_precompute(R* __restrict__ Ptab, int M, 
             }
         }
         if (pair)
-            store_pair_block<R>(Ptab, M, N, blk, lx, ly, h, scale, tid,
+            store_pair_block<R>(Ptab, M, N, pair == 2, blk, lx, ly, h, scale, tid,
                                 [&](int i, int j) { return 0.5 * (Rs[i * h + j] + Rs[j * h + i]); });
         __syncthreads();
     }
@@ -678,7 +679,7 @@ __global__ __launch_bounds__(64) void k_precompute_mfma(R* __restrict__ Ptab, in
                 if (!pair) dst[b * Eh + i * h - i * (i - 1) / 2 + (j - i)] = (R)(u * scale);
             }
         }
-        if (pair) store_pair_block<R>(Ptab, M, N, b, lx, ly, h, scale, l, at);
+        if (pair) store_pair_block<R>(Ptab, M, N, pair == 2, b, lx, ly, h, scale, l, at);
     }
     for (int off = 32; off >= 1; off >>= 1) pmax = fmax(pmax, __shfl_xor(pmax, off, 64));
     store_class_flags<R>(Ptab, M, N, Q, FS, lx, ly, !keep_all && pmax < (sizeof(R) == 4 ? 0x1p-30 : 0x1p-60), l, pair);
@@ -942,7 +943,7 @@ hipError_t launch_project(const R* psi, R* out, int M, int N, bool mean, hipStre
 
 template <class R>
 hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int nsteps, int scheme,
-                             hipStream_t st, bool keep_all, bool pair) {
+                             hipStream_t st, bool keep_all, int pair) {
     const int Q = M / 4 + 1;
     const size_t slots = table_slots(M, N);  // one workgroup per stored class
     const int h = (N & 1) ? N : N / 2;
@@ -954,15 +955,15 @@ hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int n
     if (h <= 32 && std::getenv("SE2N_SCALAR_PRECOMPUTE") == nullptr) {
         if (h <= 16)
             hipLaunchKernelGGL((k_precompute_mfma<R, 1>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
-                               flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
+                               flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair);
         else
             hipLaunchKernelGGL((k_precompute_mfma<R, 2>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
-                               flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
+                               flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_precompute<R>), dim3((unsigned)slots), dim3(64), lds, st, Ptab, M, N, Q,
                        flag_stride(M), beta,
-                       T, nsteps, scheme, scale, keep_all ? 1 : 0, pair ? 1 : 0);
+                       T, nsteps, scheme, scale, keep_all ? 1 : 0, pair);
     return hipGetLastError();
 }
 
@@ -986,7 +987,7 @@ hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int n
     template hipError_t launch_lift<R>(const R*, const uint8_t*, const uint8_t*, R*, int, int,         \
                                        hipStream_t);                                                   \
     template hipError_t launch_project<R>(const R*, R*, int, int, bool, hipStream_t);                  \
-    template hipError_t launch_precompute<R>(R*, int, int, double, double, int, int, hipStream_t, bool, bool);
+    template hipError_t launch_precompute<R>(R*, int, int, double, double, int, int, hipStream_t, bool, int);
 
 SE2N_INSTANTIATE(float)
 SE2N_INSTANTIATE(double)

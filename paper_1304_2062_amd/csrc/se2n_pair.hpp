@@ -79,20 +79,39 @@ __host__ __device__ constexpr int pair_mid_threads(int M, int hs) {
 //     T[((lx nblk + blk) Eh + e) QP + ly],  Eh = hs (hs + 1) / 2,
 // e over the packed upper triangle of the block, every class stored (no slot
 // is shared), ly padded to QP.  The flags of negligible classes follow.
-__host__ __device__ constexpr int pair_qp(int M) { return (M / 4 + 1 + 15) / 16 * 16; }
-__host__ __device__ constexpr size_t pair_table_entries(int M, int N) {
-    return (size_t)(M / 4 + 1) * table_class_entries(N) * pair_qp(M);
+// With halved columns (PairLay) the even classes come first, then the odd ones.
+__host__ __device__ constexpr int pair_qp(int M, bool halved) {
+    return (M / 4 + 1 + 15) / 16 * 16 + (halved ? 16 : 0);
 }
-__host__ __device__ constexpr size_t pair_table_bytes(int M, int N, int rsize) {
-    return pair_table_entries(M, N) * (size_t)rsize + (size_t)(M / 4 + 1) * flag_stride(M) + 64;
+__host__ __device__ constexpr int pair_odd_pos(int M) { return (M / 8 + 1 + 15) / 16 * 16; }
+__host__ __device__ constexpr int pair_class_pos(int M, bool halved, int ly) {
+    return halved ? (ly >> 1) + ((ly & 1) ? pair_odd_pos(M) : 0) : ly;
+}
+__host__ __device__ constexpr size_t pair_table_entries(int M, int N, bool halved) {
+    return (size_t)(M / 4 + 1) * table_class_entries(N) * pair_qp(M, halved);
+}
+__host__ __device__ constexpr size_t pair_table_bytes(int M, int N, int rsize, bool halved) {
+    return pair_table_entries(M, N, halved) * (size_t)rsize + (size_t)(M / 4 + 1) * flag_stride(M) + 64;
 }
 
 // Whether a side and orientation count run on the pair path: a block of a
 // column fits in the LDS of one workgroup, at most 16 elements per thread.
-__host__ __device__ constexpr bool pair_fits(int M, int N, int rsize) {
+__host__ __device__ constexpr bool pair_block_fits(int M, int N, int rsize) {
     const int hs = pair_hs(N);
-    return M <= 1024 && hs * M <= 16 * pair_max_threads(rsize) && pair_mid_threads(M, hs) <= pair_max_threads(rsize) &&
+    return hs * M <= 16 * pair_max_threads(rsize) && pair_mid_threads(M, hs) <= pair_max_threads(rsize) &&
            pair_lds_bytes(M, hs, rsize) <= (size_t)kPairLds;
+}
+__host__ __device__ constexpr bool pair_fits(int M, int N, int rsize) {
+    return M <= 1024 && pair_block_fits(M, N, rsize);
+}
+// Or half a column does: the row passes take the columns' first radix-2 step
+// (PairLay).  FP64 on the sides with compiled transforms, 1024^2, N = 32 751
+// -> 478 us against the five passes, 512^2, N = 40 308 -> 184 us, 2048^2,
+// N = 16 1500 -> 1010 us.  Not FP32: its five passes run at the memory's rate
+// (1024^2, N = 48 381 against 450 us this way, 2048^2, N = 32 755 against 1080).
+__host__ __device__ constexpr bool pair_halves(int M, int N, int rsize) {
+    return rsize == 8 && (M == 512 || M == 1024 || M == 2048) && !pair_fits(M, N, rsize) &&
+           pair_block_fits(M / 2, N, rsize);
 }
 
 // ---------------------------------------------------------------------------
@@ -206,12 +225,22 @@ __host__ __device__ constexpr int pair_last_radix(int L, int EPT) {
 // ---------------------------------------------------------------------------
 // Layout of the stored spectrum
 // ---------------------------------------------------------------------------
+// Halved columns: the first radix-2 step of a column's transform, by
+// decimation in frequency, belongs to the row passes, which hold rows n and
+// n + M/2 together.  With x the column of length M, the even frequencies are
+// the transform of length M/2 of x[n] + x[n + M/2] and the odd ones that of
+// (x[n] - x[n + M/2]) w_M^n.  A block then holds rb/2 rows n of the even half
+// followed by the same rows of the odd half, and the middle pass takes the
+// two halves of a column one by one: the classes of a column and of its
+// mirror have the same parity.
 struct PairLay {
-    int rb;  // rows per block: a power of two, or M
-    int lg;  // log2(rb), or 16 for rb = M (one block)
+    int rb;      // rows per block: a power of two, or M
+    int lg;      // log2(rb), or 16 for rb = M (one block); of rb/2 with halved columns
+    int halved;  // columns in halves
     // elements from one block to the next
     __host__ __device__ long block(int H, int N) const { return (long)N * H * rb; }
-    // offset of row y within the slice-and-column grid of its block
+    // offset of row y (of row n of the even half) within the slice-and-column
+    // grid of its block
     __host__ __device__ long row(int y, int H, int N) const {
         return (long)(y >> lg) * block(H, N) + (y - ((y >> lg) << lg));
     }
@@ -223,8 +252,8 @@ struct PairLay {
 // Transforms of a runtime number of sequences of a compiled length
 // ---------------------------------------------------------------------------
 // One Stockham stage over nt transforms of length L: in(t, j, v) fetches the
-// inputs j + r L/RADIX of butterfly j of transform t, out(t, o, v) takes its
-// outputs o + r NS.  `fence`: a barrier between the two, for stages that read
+// inputs j + r L/RADIX of butterfly j of transform t, out(t, o, v, i) takes its
+// outputs o + r NS (i: the thread's i-th butterfly).  `fence`: a barrier between the two, for stages that read
 // and write the same LDS buffer.  nt L <= EPT nthr.
 template <class R, int RADIX, bool INV, int L, int NS, int EPT, class In, class Out>
 __device__ __forceinline__ void pair_stage(const C2<R>* tw, int nt, int tid, int nthr, In&& in, Out&& out,
@@ -253,7 +282,7 @@ __device__ __forceinline__ void pair_stage(const C2<R>* tw, int nt, int tid, int
             const int k = j - q * NS;
             if (NS > 1) pair_twiddles<R, RADIX, INV>(v[i], tw, k * TWSTEP, L / 4);
             pair_dft<R, RADIX, INV>(v[i]);
-            out(t, q * NS * RADIX + k, v[i]);
+            out(t, q * NS * RADIX + k, v[i], i);
         }
     }
 }
@@ -266,7 +295,7 @@ __device__ __forceinline__ int pair_pos(int M, int t, int i) {
 }
 
 // Stages S .. of the transforms held in buf.  `first(t, j, v)` replaces the
-// LDS read of stage 0 (Identity: read LDS), `last(t, o, v, NSTEP)` the LDS
+// LDS read of stage 0 (Identity: read LDS), `last(t, o, v, i)` the LDS
 // write of the last stage (Identity: write LDS).  Ends with a barrier exactly
 // when the result is in LDS.
 struct PairLds {};
@@ -294,7 +323,7 @@ __device__ __forceinline__ void pair_fft_from(C2<R>* buf, const C2<R>* tw, int n
                 first(t, j, v);
             }
         };
-        auto out = [&](int t, int o, C2<R>* v) {
+        auto out = [&](int t, int o, C2<R>* v, int i) {
             if constexpr (OUT_LDS) {
                 C2<R>* pb = buf + t * pair_stride(L);
                 if constexpr (pad_linear_write(NS, RADIX, 32)) {
@@ -306,7 +335,7 @@ __device__ __forceinline__ void pair_fft_from(C2<R>* buf, const C2<R>* tw, int n
                     for (int r = 0; r < RADIX; ++r) pb[lds_pad(o + r * NS)] = v[r];
                 }
             } else {
-                last(t, o, v);
+                last(t, o, v, i);
             }
         };
         pair_stage<R, RADIX, INV, L, NS, EPT>(tw, nt, tid, nthr, in, out, IN_LDS);
@@ -344,17 +373,25 @@ __device__ __forceinline__ void pair_fft(C2<R>* buf, const C2<R>* tw, int M, int
 // registers read 1 byte per multiply-add and were bound by it (1024^2, N = 32:
 // 64 us of the pass, 28 us this way).  Classes 0 and M/4 have two modes each
 // and share the position v = 0.  Negligible classes give zeros unread.
-template <class R, int RPT, int MS>
+//
+// HALF: M is the length of the half columns of parity `par`, whose position k
+// is the mode 2k + par of the column: the even half looks like a column of
+// side M, in the odd half class 2v + 1 holds k = v, M/2 + v, M/2 - 1 - v and
+// M - 1 - v.
+template <class R, int RPT, int MS, bool HALF = false>
 __device__ __forceinline__ void pair_solve(C2<R>* buf, const R* __restrict__ T, const uint8_t* __restrict__ flags,
-                                           int M_, int N, int kx, int blk, int tid) {
+                                           int M_, int N, int kx, int blk, int tid, int par = 0) {
     const int M = MS ? MS : M_;
     const int H = M >> 1, M4 = M >> 2;
     const int hs = pair_hs(N);
     const int Eh = hs * (hs + 1) / 2;
-    const int QP = pair_qp(M);
-    const int lx = kx <= M4 ? kx : H - kx;
-    const R* __restrict__ Tb = T + (size_t)(lx * pair_nblk(N) + blk) * Eh * QP;
-    const uint8_t* __restrict__ fl = flags + (size_t)lx * flag_stride(M);
+    const int MF = HALF ? 2 * M : M;  // the side
+    const int QP = pair_qp(MF, HALF);
+    const int lx = kx <= MF / 4 ? kx : MF / 2 - kx;
+    const R* __restrict__ Tb =
+        T + (size_t)(lx * pair_nblk(N) + blk) * Eh * QP + (HALF && par ? pair_odd_pos(MF) : 0);
+    const uint8_t* __restrict__ fl = flags + (size_t)lx * flag_stride(MF);
+    const bool odd_half = HALF && par;
     const bool flip0 = blk == 1;
 
     int part = tid / M4;
@@ -363,9 +400,10 @@ __device__ __forceinline__ void pair_solve(C2<R>* buf, const R* __restrict__ T, 
     const int i0 = part * RPT;
     const bool act = i0 < hs;
     // modes 0, 1: class v; modes 2, 3: class v again, or M/4 at v = 0
-    const int lb = v == 0 ? M4 : v;
-    const int ky[4] = {v, H + v, H - lb, v == 0 ? H + M4 : M - v};
-    const bool live0 = act && !fl[v], live1 = act && !fl[lb];
+    const int lb = v == 0 && !odd_half ? M4 : v;
+    const int down = odd_half ? v + 1 : lb;
+    const int ky[4] = {v, H + v, H - down, v == 0 && !odd_half ? H + M4 : M - down};
+    const bool live0 = act && !fl[HALF ? 2 * v + par : v], live1 = act && !fl[HALF ? 2 * lb + par : lb];
     C2<R> y[4][RPT];
 #pragma unroll
     for (int m = 0; m < 4; ++m)
@@ -406,7 +444,7 @@ __device__ __forceinline__ void pair_solve(C2<R>* buf, const R* __restrict__ T, 
         }
     };
     if (live0 || live1) {
-        if (__any(v == 0)) walk(std::true_type{});
+        if (!odd_half && __any(v == 0)) walk(std::true_type{});
         else walk(std::false_type{});
     }
     __syncthreads();  // every column is read before any row is replaced
@@ -437,23 +475,24 @@ __device__ __forceinline__ C2<R>* pair_col(C2<R>* spec, const PairLay& lay, int 
 }
 
 // The stage-0 inputs of a column block of a compiled side, in registers.
-template <class R, int MS, int EPT>
+// (H: columns; a half column's length MS is H, a column's 2H)
+template <class R, int MS, int EPT, int H = MS / 2>
 struct PairMidIn {
     static constexpr int R0 = pair_radix(MS, EPT, 0);
     static constexpr int NB = MS / R0;
     static constexpr int MAXB = (EPT + R0 - 1) / R0;
     C2<R> v[MAXB][R0];
-    // rows j + r NB: NB is a multiple of every rb < M that a plan takes
+    // rows j + r NB: NB is a multiple of every block's rows < M that a plan takes
     __device__ __forceinline__ void load(const C2<R>* __restrict__ col, long step, const PairLay& lay, int N, int hs,
                                          int tid, int nthr) {
         const int total = NB * hs;
-        const long rstep = lay.row(NB, MS / 2, N);
+        const long rstep = lay.row(NB, H, N);
 #pragma unroll
         for (int i = 0; i < MAXB; ++i) {
             const int b = tid + i * nthr;
             if (b < total) {
                 const int t = b / NB;
-                const C2<R>* g = col + t * step + lay.row(b - t * NB, MS / 2, N);
+                const C2<R>* g = col + t * step + lay.row(b - t * NB, H, N);
 #pragma unroll
                 for (int r = 0; r < R0; ++r) v[i][r] = g[r * rstep];
             }
@@ -486,22 +525,23 @@ struct PairMidIn {
 // The rest of a column block of a compiled side, the stage-0 inputs in `in`:
 // `next` runs before the inverse transform, whose last stage stores the
 // column from registers (no LDS is read after its barrier).
-template <class R, int MS, int EPT, class Next>
-__device__ __forceinline__ void pair_mid_run(PairMidIn<R, MS, EPT>& in, C2<R>* __restrict__ col, long step,
+template <class R, int MS, int EPT, bool HALF = false, class In, class Next>
+__device__ __forceinline__ void pair_mid_run(In& in, C2<R>* __restrict__ col, long step,
                                              const PairLay& lay, const R* __restrict__ T, int N, int kx, int blk, const C2<R>* tw,
-                                             C2<R>* buf, int tid, int nthr, Next&& next) {
+                                             C2<R>* buf, int tid, int nthr, Next&& next, int par = 0) {
     constexpr int RL = pair_last_radix(MS, EPT);
+    constexpr int MF = HALF ? 2 * MS : MS;
     const int hs = pair_hs(N);
-    const uint8_t* flags = reinterpret_cast<const uint8_t*>(T + pair_table_entries(MS, N));
+    const uint8_t* flags = reinterpret_cast<const uint8_t*>(T + pair_table_entries(MF, N, HALF));
     in.stage0(buf, hs, tid, nthr);
     __syncthreads();
-    pair_fft_from<R, false, MS, EPT, 1, PairMidIn<R, MS, EPT>::R0>(buf, tw, hs, tid, nthr, PairLds{}, PairLds{});
-    pair_solve<R, EPT / 4, MS>(buf, T, flags, MS, N, kx, blk, tid);
+    pair_fft_from<R, false, MS, EPT, 1, In::R0>(buf, tw, hs, tid, nthr, PairLds{}, PairLds{});
+    pair_solve<R, EPT / 4, MS, HALF>(buf, T, flags, MS, N, kx, blk, tid, par);
     __syncthreads();
     next();
-    const long rstep = lay.row(MS / RL, MS / 2, N);
-    pair_fft_from<R, true, MS, EPT, 0, 1>(buf, tw, hs, tid, nthr, PairLds{}, [&](int t, int o, C2<R>* w) {
-        C2<R>* g = col + t * step + lay.row(o, MS / 2, N);
+    const long rstep = lay.row(MS / RL, MF / 2, N);
+    pair_fft_from<R, true, MS, EPT, 0, 1>(buf, tw, hs, tid, nthr, PairLds{}, [&](int t, int o, C2<R>* w, int) {
+        C2<R>* g = col + t * step + lay.row(o, MF / 2, N);
 #pragma unroll
         for (int r = 0; r < RL; ++r) g[r * rstep] = w[r];
     });
@@ -515,7 +555,7 @@ __device__ __forceinline__ void pair_mid_generic(C2<R>* __restrict__ spec, const
     const int hs = pair_hs(N);
     long step;
     C2<R>* col = pair_col<R>(spec, lay, M, N, kx, blk, step);
-    const uint8_t* flags = reinterpret_cast<const uint8_t*>(T + pair_table_entries(M, N));
+    const uint8_t* flags = reinterpret_cast<const uint8_t*>(T + pair_table_entries(M, N, false));
     const float inv_M = 1.0f / (float)M;
     for (int e = tid; e < hs * M; e += nthr) {
         const int t = fdiv(e, inv_M);
@@ -538,7 +578,8 @@ __device__ __forceinline__ void pair_mid_generic(C2<R>* __restrict__ spec, const
 // go to the 8 XCDs in turn) takes a contiguous range of class rows lx, and of
 // each row the columns lx and M/2 - lx back to back, so that one L2 serves the
 // second's propagators and sees neighbouring columns together; columns 0
-// (with M/2) and M/4 are their own partners and pair up.
+// (with M/2) and M/4 are their own partners and pair up.  The two halves of a
+// column (par) are neighbours: they share its lines.
 __host__ __device__ inline void pair_mid_col(int i, int H, int nblk, int& kx, int& blk) {
     const int per = H / 2;
     const int w = xcd_contiguous(i, H * nblk);
@@ -546,6 +587,15 @@ __host__ __device__ inline void pair_mid_col(int i, int H, int nblk, int& kx, in
     const int lx = unit % per;
     blk = unit / per;
     kx = (w & 1) == 0 ? lx : (lx == 0 ? H / 2 : H - lx);
+}
+__host__ __device__ inline void pair_mid_half(int i, int H, int nblk, int& kx, int& blk, int& par) {
+    const int per = H / 2;
+    const int w = xcd_contiguous(i, 2 * H * nblk);
+    const int unit = w >> 2;
+    const int lx = unit % per;
+    blk = unit / per;
+    par = w & 1;
+    kx = (w & 2) == 0 ? lx : (lx == 0 ? H / 2 : H - lx);
 }
 
 // ---------------------------------------------------------------------------
@@ -669,10 +719,117 @@ __device__ __forceinline__ void pair_pack(C2<R>* buf, const C2<R>* __restrict__ 
     }
 }
 
+// The tile's rows with halved columns: `rows` / 2 rows y0 .. and the same
+// number from M/2 + y0 on.
+template <bool HALF>
+__device__ __forceinline__ int pair_image_row(int M, int rows, int y0, int row) {
+    return y0 + row + (HALF && row >= (rows >> 1) ? (M >> 1) - (rows >> 1) : 0);
+}
+
+// pair_unpack with halved columns: a lane takes one row n and n + M/2, and its
+// twiddle w_M^n serves every column.
+template <class R, int MS>
+__device__ __forceinline__ void pair_unpack_half(const C2<R>* buf, C2<R>* __restrict__ spec, const PairLay& lay, int N,
+                                                 int t, int rows, int y0, const C2<R>* tw, int tid, int nthr) {
+    constexpr int H = MS >> 1;
+    const int r2 = rows >> 1;
+    const int sh = __ffs(r2) - 1;
+    const int r = tid & (r2 - 1);
+    const bool has_b = 2 * t + 1 < N;
+    const int odd = lay.rb / 2;  // from the even half's entry to the odd half's
+    const R half = R(0.5);
+    C2<R>* sa = spec + lay.row(y0, H, N) + lay.col(2 * t, 0, H) + r;
+    const long plane = lay.col(1, 0, H);
+    const C2<R> w = tw[tw_pos(y0 + r)];
+    auto split = [&](int row, int k, C2<R>& a, C2<R>& b) {
+        const C2<R> z = buf[pair_pos<MS>(MS, row, k)];
+        const C2<R> u = buf[pair_pos<MS>(MS, row, k == 0 ? H : MS - k)];
+        if (k == 0) {
+            a = cmk<R>(z.x, u.x);
+            b = cmk<R>(z.y, u.y);
+        } else {
+            a = cmk<R>(half * (z.x + u.x), half * (z.y - u.y));
+            b = cmk<R>(half * (z.y + u.y), half * (u.x - z.x));
+        }
+    };
+    for (int k = tid >> sh; k < H; k += nthr >> sh) {
+        C2<R> a0, b0, a1, b1;
+        split(r, k, a0, b0);
+        split(r + r2, k, a1, b1);
+        C2<R>* p = sa + (size_t)k * lay.rb;
+        p[0] = cmk<R>(a0.x + a1.x, a0.y + a1.y);
+        p[odd] = cmul<R>(cmk<R>(a0.x - a1.x, a0.y - a1.y), w);
+        if (has_b) {
+            p[plane] = cmk<R>(b0.x + b1.x, b0.y + b1.y);
+            p[plane + odd] = cmul<R>(cmk<R>(b0.x - b1.x, b0.y - b1.y), w);
+        }
+    }
+}
+
+// The inverse of pair_unpack_half in two steps, so that the loads can be in
+// flight behind a transform; rows MS <= EPT nthr.
+template <class R, int MS, int EPT>
+struct PairHalfIn {
+    static constexpr int H = MS >> 1;
+    static constexpr int NV = EPT / 4;  // columns per thread, four values each
+    C2<R> a0[NV], a1[NV], b0[NV], b1[NV];
+    __device__ __forceinline__ void load(const C2<R>* __restrict__ spec, const PairLay& lay, int N, int t, int rows,
+                                         int y0, int tid, int nthr) {
+        const int r2 = rows >> 1;
+        const int sh = __ffs(r2) - 1;
+        const C2<R>* base = spec + lay.row(y0, H, N) + lay.col(2 * t, 0, H) + (tid & (r2 - 1));
+        const long plane = lay.col(1, 0, H);
+        const bool has_b = 2 * t + 1 < N;
+        const int odd = lay.rb / 2;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int k = (tid + i * nthr) >> sh;
+            if (k < H) {
+                const C2<R>* p = base + (size_t)k * lay.rb;
+                a0[i] = p[0];
+                a1[i] = p[odd];
+                b0[i] = b1[i] = cmk<R>(R(0), R(0));
+                if (has_b) {
+                    b0[i] = p[plane];
+                    b1[i] = p[plane + odd];
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store(C2<R>* buf, int rows, int y0, const C2<R>* tw, int tid, int nthr) {
+        const int r2 = rows >> 1;
+        const int sh = __ffs(r2) - 1;
+        const int r = tid & (r2 - 1);
+        auto put = [&](int tr, int k, C2<R> a, C2<R> b) {
+            C2<R> z, w;
+            if (k == 0) {
+                z = cmk<R>(a.x, b.x);
+                w = cmk<R>(a.y, b.y);
+            } else {
+                z = cmk<R>(a.x - b.y, a.y + b.x);
+                w = cmk<R>(a.x + b.y, b.x - a.y);
+            }
+            buf[pair_pos<MS>(MS, tr, k)] = z;
+            buf[pair_pos<MS>(MS, tr, k == 0 ? H : MS - k)] = w;
+        };
+        C2<R> w = tw[tw_pos(y0 + r)];
+        w.y = -w.y;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int k = (tid + i * nthr) >> sh;
+            if (k < H) {
+                const C2<R> da = cmul<R>(a1[i], w), db = cmul<R>(b1[i], w);
+                put(r, k, cmk<R>(a0[i].x + da.x, a0[i].y + da.y), cmk<R>(b0[i].x + db.x, b0[i].y + db.y));
+                put(r + r2, k, cmk<R>(a0[i].x - da.x, a0[i].y - da.y), cmk<R>(b0[i].x - db.x, b0[i].y - db.y));
+            }
+        }
+    }
+};
+
 // Forward row pass of pair t over rows y0 .. y0 + rows - 1.
 //   PSRC_LIFT    f (1 - mask) at the pixel's orientation (rmap)
 //   PSRC_VOLUME  real volume vol[N][M][M]
-template <class R, int SRC, int MS, int EPT>
+template <class R, int SRC, int MS, int EPT, bool HALF = false>
 __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uint8_t* __restrict__ mask,
                                               const uint8_t* __restrict__ rmap, const R* __restrict__ vol,
                                               C2<R>* __restrict__ spec, const PairLay& lay, int M_, int N, int rows,
@@ -695,7 +852,7 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
         return z;
     };
     auto from_volume = [&](int t, int row, int n) {
-        const size_t p = (size_t)(y0 + row) * M + n;
+        const size_t p = (size_t)pair_image_row<HALF>(M, rows, y0, row) * M + n;
         if (odd) {
             const R a = vol[(size_t)(2 * t) * img + p];
             const R b = 2 * t + 1 < N ? vol[(size_t)(2 * t + 1) * img + p] : R(0);
@@ -721,7 +878,7 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
                 for (int r = 0; r < (R0 + 3) / 4; ++r) rv[i][r] = 0;
                 if (b < NB * rows) {
                     const int row = b / NB;
-                    const size_t p = (size_t)(y0 + row) * MS + (b - row * NB);
+                    const size_t p = (size_t)pair_image_row<HALF>(M, rows, y0, row) * MS + (b - row * NB);
 #pragma unroll
                     for (int r = 0; r < R0; ++r) {
                         const R v = f[p + r * NB];
@@ -764,7 +921,8 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
             }
             __syncthreads();
             pair_fft_from<R, false, MS, EPT, 1, R0>(buf, tw, rows, tid, nthr, PairLds{}, PairLds{});
-            pair_unpack<R, MS>(buf, spec, lay, M, N, t, 0, rows, y0, tid, nthr);
+            if constexpr (HALF) pair_unpack_half<R, MS>(buf, spec, lay, N, t, rows, y0, tw, tid, nthr);
+            else pair_unpack<R, MS>(buf, spec, lay, M, N, t, 0, rows, y0, tid, nthr);
             __syncthreads();
         }
     } else {
@@ -869,6 +1027,72 @@ __device__ __forceinline__ void pair_inv_tile(C2<R>* __restrict__ spec, const Pa
                 // 1/2 of x = (p +- q) / 2)
                 pair_unpack<R, MS>(buf, spec, lay, M, N, t0 + g, g * rows, rows, y0, tid, nthr,
                                    odd ? R(1) : R(2));
+        }
+    }
+}
+
+// The same with halved columns, one pair per round: PDST_MAX, PDST_SUM or
+// PDST_VOLUME.  The next pair's rows are fetched while this one is transformed
+// (there is a workgroup per compute unit, no other hides its latency), and a
+// pixel's running value stays in the registers of the thread whose last
+// butterfly produces it.  1024^2, N = 32, FP64: 212 -> 106 us against the five
+// passes' kernel (268 MB, 2.5 TB/s); two workgroups per unit of half the rows
+// each take as long.
+template <class R, int DST, int MS, int EPT>
+__device__ __forceinline__ void pair_inv_half_tile(const C2<R>* __restrict__ spec, const PairLay& lay,
+                                                   R* __restrict__ out, int N, int rows, int y0, int t_begin,
+                                                   int t_end, const C2<R>* tw, C2<R>* buf, int tid, int nthr) {
+    constexpr int M = MS;
+    constexpr int RL = pair_last_radix(MS, EPT);
+    constexpr int NB = MS / RL;
+    constexpr int MAXB = (EPT + RL - 1) / RL;
+    const int h = N >> 1;
+    const bool odd = N & 1;
+    const size_t img = (size_t)M * M;
+    PairHalfIn<R, MS, EPT> in;
+    in.load(spec, lay, N, t_begin, rows, y0, tid, nthr);
+    R acc[MAXB][RL];
+#pragma unroll
+    for (int i = 0; i < MAXB; ++i)
+#pragma unroll
+        for (int r = 0; r < RL; ++r) acc[i][r] = DST == PDST_SUM ? R(0) : -INFINITY;
+    for (int t = t_begin; t < t_end; ++t) {
+        in.store(buf, rows, y0, tw, tid, nthr);
+        __syncthreads();
+        if (t + 1 < t_end) in.load(spec, lay, N, t + 1, rows, y0, tid, nthr);
+        const bool two = !odd || 2 * t + 1 < N;
+        pair_fft_from<R, true, MS, EPT, 0, 1>(buf, tw, rows, tid, nthr, PairLds{}, [&](int row, int o, C2<R>* v, int i) {
+            if constexpr (DST == PDST_VOLUME) {
+                R* q = out + (size_t)pair_image_row<true>(M, rows, y0, row) * M + o;
+                R* qa = q + (size_t)(odd ? 2 * t : t) * img;
+                R* qb = q + (size_t)(odd ? 2 * t + 1 : t + h) * img;
+#pragma unroll
+                for (int r = 0; r < RL; ++r) {
+                    qa[r * NB] = odd ? v[r].x : v[r].x + v[r].y;
+                    if (two) qb[r * NB] = odd ? v[r].y : v[r].x - v[r].y;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < RL; ++r) {
+                    if (DST == PDST_MAX)
+                        acc[i][r] = vmax<R>(acc[i][r], odd ? (two ? vmax<R>(v[r].x, v[r].y) : v[r].x)
+                                                           : v[r].x + fabs(v[r].y));
+                    else acc[i][r] += odd ? (two ? v[r].x + v[r].y : v[r].x) : R(2) * v[r].x;
+                }
+            }
+        });
+        __syncthreads();
+    }
+    if constexpr (DST != PDST_VOLUME) {
+#pragma unroll
+        for (int i = 0; i < MAXB; ++i) {
+            const int b = tid + i * nthr;
+            if (b < NB * rows) {
+                const int row = b / NB;
+                R* q = out + (size_t)pair_image_row<true>(M, rows, y0, row) * M + (b - row * NB);
+#pragma unroll
+                for (int r = 0; r < RL; ++r) q[r * NB] = DST == PDST_SUM ? acc[i][r] * (R(1) / (R)N) : acc[i][r];
+            }
         }
     }
 }
@@ -985,21 +1209,42 @@ __host__ __device__ constexpr int pair_fwd_rows(int M, int rsize) {
 // wave that is partly empty where halving the rows avoids it (768^2), and as
 // many pairs per round as leave the workgroups of a unit resident together
 // (768^2, N = 24: three of 6 pairs 24 us, two of 12 pairs 35 us).
+//
+// Halved columns (FP64): a tile's rows n and n + M/2 are half as many of each,
+// one workgroup lifts every pair where the tiles fill the units (1024^2,
+// N = 32: 104 -> 98 us), the projection halves its tiles until they do (512^2,
+// N = 40: 193 -> 184 us).  Blocks of 4 or 16 rows: 482 -> 559 and 493 us for
+// the whole of 1024^2, N = 32.
 inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     PairGeom g{};
     const int np = pair_count(N);
     g.lay.rb = M % 8 == 0 ? 8 : 4;
     g.lay.lg = M % 8 == 0 ? 3 : 2;
     const int most = pair_max_threads(rsize);
+    g.lay.halved = pair_halves(M, N, rsize);
+    g.lay.lg -= g.lay.halved;
     const int rows = pair_fwd_rows(M, rsize);
     g.fwd_rows = rows;
     g.fwd_ept = pair_row_ept(rows * M, rsize);
     g.fwd_threads = pair_threads(rows * M, g.fwd_ept);
     const int blocks = M / rows;
-    int ppw = 1;
+    int ppw = g.lay.halved && blocks >= num_cu ? np : 1;
     while (ppw < np && (long)blocks * ((np + ppw - 1) / ppw) > 4L * num_cu) ++ppw;
     g.fwd_pairs = ppw;
     g.vol_pairs = 1;
+    if (g.lay.halved) {
+        g.inv_rows = rows;
+        while (g.inv_rows > 2 && M / g.inv_rows < num_cu) g.inv_rows >>= 1;
+        g.inv_G = 1;
+        g.inv_ept = g.fwd_ept;
+        g.inv_threads = pair_threads(g.inv_rows * M, g.inv_ept);
+        const int hs = pair_hs(N);
+        g.mid_ept = pair_mid_ept(hs * M / 2);
+        g.mid_threads = pair_mid_threads(M / 2, hs);
+        g.mid_grid = M * pair_nblk(N);
+        if (2 * pair_lds_bytes(M / 2, hs, rsize) > (size_t)kPairLds && g.mid_grid > num_cu) g.mid_grid = num_cu;
+        return g;
+    }
     int r = rows;
     while (r > 1 && M / r < num_cu) r >>= 1;
     while (r > 1 && M / r % num_cu != 0) r >>= 1;

@@ -61,6 +61,73 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_mid(C
     }
 }
 
+// Half columns (PairLay), side 2 MS.  1024^2, N = 32, FP64: 355 -> 237 us
+// against the two column passes and the solve (268 MB read and written and 152
+// MB of propagators, 3 TB/s); a workgroup each instead of walkers: 509 against
+// 483 us for the whole.
+template <class R, int MS, int EPT, bool WALK>
+__global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_mid_half(
+    C2<R>* __restrict__ spec, PairLay lay, const R* __restrict__ T, int N, const C2<R>* __restrict__ twg) {
+    extern __shared__ unsigned char smem_raw[];
+    C2<R>* tw = reinterpret_cast<C2<R>*>(smem_raw);
+    C2<R>* buf = tw + pair_tw_elems(MS);
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    const int nblk = pair_nblk(N);
+    const int nt = 2 * MS * nblk;
+    const int hs = pair_hs(N);
+    PairMidIn<R, MS, EPT, MS> in;
+    int kx, blk, par;
+    long step;
+    auto column = [&](int i) {
+        pair_mid_half(i, MS, nblk, kx, blk, par);
+        return pair_col<R>(spec, lay, 2 * MS, N, kx, blk, step) + par * (lay.rb / 2);
+    };
+    C2<R>* col = column(blockIdx.x);
+    in.load(col, step, lay, N, hs, tid, nthr);
+    // the table of length 2 MS, every other entry
+    for (int m = tid; m < MS / 4; m += nthr) {
+        const C2<R> w = twg[2 * m];
+        tw[tw_pos(m)] = w;
+        tw[tw_pos(m + MS / 4)] = cmk<R>(w.y, -w.x);
+        tw[tw_pos(m + MS / 2)] = cmk<R>(-w.x, -w.y);
+    }
+    for (int i = blockIdx.x;; i += gridDim.x) {
+        const bool more = WALK && i + (int)gridDim.x < nt;
+        const int k0 = kx, b0 = blk, p0 = par;
+        C2<R>* cn = col;
+        if (more) cn = column(i + gridDim.x);
+        pair_mid_run<R, MS, EPT, true>(
+            in, col, step, lay, T, N, k0, b0, tw, buf, tid, nthr,
+            [&] {
+                if (more) in.load(cn, step, lay, N, hs, tid, nthr);
+            },
+            p0);
+        if (!more) return;
+        col = cn;
+    }
+}
+
+template <class R, int MS, int EPT>
+hipError_t mid_half_go(C2<R>* spec, const R* T, int N, const PairGeom& g, const C2<R>* tw, hipStream_t st) {
+    const int tiles = 2 * MS * pair_nblk(N);
+    const size_t lds = pair_lds_bytes(MS, pair_hs(N), (int)sizeof(R));
+    if constexpr (EPT == 16) {
+        if (g.mid_grid < tiles) {
+            hipLaunchKernelGGL((k_pair_mid_half<R, MS, EPT, true>), dim3((unsigned)g.mid_grid), dim3(g.mid_threads),
+                               lds, st, spec, g.lay, T, N, tw);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_pair_mid_half<R, MS, EPT, false>), dim3((unsigned)tiles), dim3(g.mid_threads), lds, st, spec,
+                       g.lay, T, N, tw);
+    return hipGetLastError();
+}
+template <class R, int MS>
+hipError_t mid_half(C2<R>* spec, const R* T, int N, const PairGeom& g, const C2<R>* tw, hipStream_t st) {
+    if (g.mid_ept == 8) return mid_half_go<R, MS, 8>(spec, T, N, g, tw, st);
+    return mid_half_go<R, MS, 16>(spec, T, N, g, tw, st);
+}
+
 template <class R, int MS, int EPT>
 hipError_t mid_go(C2<R>* spec, const R* T, int M, int N, const PairGeom& g, const FftPlan& planM, const C2<R>* tw,
                   hipStream_t st) {
@@ -91,6 +158,13 @@ hipError_t mid_side(C2<R>* spec, const R* T, int M, int N, const PairGeom& g, co
 template <class R>
 hipError_t launch_pair_mid(C2<R>* spec, const R* T, int M, int N, const PairGeom& g, const FftPlan& planM,
                            const C2<R>* tw, hipStream_t st) {
+    if constexpr (sizeof(R) == 8) {
+        if (g.lay.halved) {
+            if (M == 512) return mid_half<R, 256>(spec, T, N, g, tw, st);
+            if (M == 1024) return mid_half<R, 512>(spec, T, N, g, tw, st);
+            return mid_half<R, 1024>(spec, T, N, g, tw, st);
+        }
+    }
     switch (M) {
 #define SE2N_SIDE(m) \
     case m: return mid_side<R, m>(spec, T, M, N, g, planM, tw, st);

@@ -8,7 +8,8 @@ namespace se2n {
 
 namespace {
 
-template <class R, int SRC, int MS, int EPT>
+// HALF: halved columns (PairLay)
+template <class R, int SRC, int MS, int EPT, bool HALF>
 __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_fwd(const R* __restrict__ f, const uint8_t* __restrict__ mask,
                                                    const uint8_t* __restrict__ rmap, const R* __restrict__ vol,
                                                    C2<R>* __restrict__ spec, PairLay lay, int M_, int N, int rows, int ppw,
@@ -25,8 +26,8 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_fwd(c
     // row blocks fastest: neighbours on one XCD complete each other's lines
     const int grp = w / nrb, rb = w - grp * nrb;
     const int t0 = grp * ppw;
-    pair_fwd_tile<R, SRC, MS, EPT>(f, mask, rmap, vol, spec, lay, M, N, rows, rb * rows, t0, min(pair_count(N), t0 + ppw),
-                                   planM, tw, buf, tid, nthr);
+    pair_fwd_tile<R, SRC, MS, EPT, HALF>(f, mask, rmap, vol, spec, lay, M, N, rows, rb * (HALF ? rows / 2 : rows), t0,
+                                         min(pair_count(N), t0 + ppw), planM, tw, buf, tid, nthr);
 }
 
 template <class R, int DST, int MS, int EPT>
@@ -46,6 +47,24 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_inv(C
     const int t0 = grp * ppw;
     pair_inv_tile<R, DST, MS, EPT>(spec, lay, out, hmax, f, mask, eps, M, N, rows, G, rb * rows, t0,
                                    min(pair_count(N), t0 + ppw), planM, tw, buf, tid, nthr);
+}
+
+template <class R, int DST, int MS, int EPT>
+__global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_inv_half(
+    const C2<R>* __restrict__ spec, PairLay lay, R* __restrict__ out, int N, int rows, int ppw,
+    const C2<R>* __restrict__ twg) {
+    extern __shared__ unsigned char smem_raw[];
+    C2<R>* tw = reinterpret_cast<C2<R>*>(smem_raw);
+    C2<R>* buf = tw + pair_tw_elems(MS);
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    pair_load_tw<R>(tw, twg, MS, tid, nthr);
+    __syncthreads();
+    const int nrb = MS / rows;
+    const int w = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int grp = w / nrb, rb = w - grp * nrb;
+    const int t0 = grp * ppw;
+    pair_inv_half_tile<R, DST, MS, EPT>(spec, lay, out, N, rows, rb * (rows / 2), t0, min(pair_count(N), t0 + ppw), tw,
+                                        buf, tid, nthr);
 }
 
 template <class R, int MS, int EPT>
@@ -80,6 +99,13 @@ hipError_t by_side(int M, F&& f) {
     }
     return f(std::integral_constant<int, 0>{});
 }
+// The sides whose columns may be halved (pair_halves).
+template <class F>
+hipError_t by_half_side(int M, F&& f) {
+    if (M == 512) return f(std::integral_constant<int, 512>{});
+    if (M == 1024) return f(std::integral_constant<int, 1024>{});
+    return f(std::integral_constant<int, 2048>{});
+}
 template <class F>
 hipError_t by_ept(int ept, F&& f) {
     return ept == 8 ? f(std::integral_constant<int, 8>{}) : f(std::integral_constant<int, 16>{});
@@ -93,16 +119,29 @@ hipError_t launch_pair_fwd(int src, const R* f, const uint8_t* mask, const uint8
     const int np = pair_count(N);
     const dim3 grid((unsigned)(M / g.fwd_rows * ((np + g.fwd_pairs - 1) / g.fwd_pairs)));
     const size_t lds = pair_lds_bytes(M, g.fwd_rows, (int)sizeof(R));
+    if constexpr (sizeof(R) == 8) {
+        if (g.lay.halved) return by_half_side(M, [&](auto ms) {
+            constexpr int MS = decltype(ms)::value;
+            constexpr int EPT = pair_row_ept(pair_fwd_rows(MS, (int)sizeof(R)) * MS, (int)sizeof(R));
+            if (src == PSRC_LIFT)
+                hipLaunchKernelGGL((k_pair_fwd<R, PSRC_LIFT, MS, EPT, true>), grid, dim3(g.fwd_threads), lds, st, f,
+                                   mask, rmap, vol, spec, g.lay, M, N, g.fwd_rows, g.fwd_pairs, planM, tw);
+            else
+                hipLaunchKernelGGL((k_pair_fwd<R, PSRC_VOLUME, MS, EPT, true>), grid, dim3(g.fwd_threads), lds, st, f,
+                                   mask, rmap, vol, spec, g.lay, M, N, g.fwd_rows, g.fwd_pairs, planM, tw);
+            return hipGetLastError();
+        });
+    }
     return by_side<R>(M, [&](auto ms) {
         return by_ept(g.fwd_ept, [&](auto ept) {
             constexpr int MS = decltype(ms)::value, EPT = decltype(ept)::value;
             constexpr int rs = (int)sizeof(R);
             if constexpr (MS == 0 || EPT == pair_row_ept(pair_fwd_rows(MS ? MS : 16, rs) * MS, rs)) {
                 if (src == PSRC_LIFT)
-                    hipLaunchKernelGGL((k_pair_fwd<R, PSRC_LIFT, MS, EPT>), grid, dim3(g.fwd_threads), lds, st, f, mask,
+                    hipLaunchKernelGGL((k_pair_fwd<R, PSRC_LIFT, MS, EPT, false>), grid, dim3(g.fwd_threads), lds, st, f, mask,
                                        rmap, vol, spec, g.lay, M, N, g.fwd_rows, g.fwd_pairs, planM, tw);
                 else
-                    hipLaunchKernelGGL((k_pair_fwd<R, PSRC_VOLUME, MS, EPT>), grid, dim3(g.fwd_threads), lds, st, f,
+                    hipLaunchKernelGGL((k_pair_fwd<R, PSRC_VOLUME, MS, EPT, false>), grid, dim3(g.fwd_threads), lds, st, f,
                                        mask, rmap, vol, spec, g.lay, M, N, g.fwd_rows, g.fwd_pairs, planM, tw);
                 return hipGetLastError();
             } else {
@@ -122,6 +161,20 @@ hipError_t launch_pair_inv(int dst, C2<R>* spec, R* out, int M, int N, const Pai
     const int ppw = vol ? g.vol_pairs : np;
     const int threads = vol ? g.fwd_threads : g.inv_threads;
     const dim3 grid((unsigned)(M / rows * ((np + ppw - 1) / ppw)));
+    if constexpr (sizeof(R) == 8) {
+        if (g.lay.halved) return by_half_side(M, [&](auto ms) {
+            constexpr int MS = decltype(ms)::value;
+            constexpr int EPT = pair_row_ept(pair_fwd_rows(MS, (int)sizeof(R)) * MS, (int)sizeof(R));
+            const size_t lds = pair_lds_bytes(MS, rows, (int)sizeof(R));
+#define SE2N_INV(D) \
+    hipLaunchKernelGGL((k_pair_inv_half<R, D, MS, EPT>), grid, dim3(threads), lds, st, spec, g.lay, out, N, rows, ppw, tw)
+            if (dst == PDST_MAX) SE2N_INV(PDST_MAX);
+            else if (dst == PDST_SUM) SE2N_INV(PDST_SUM);
+            else SE2N_INV(PDST_VOLUME);
+#undef SE2N_INV
+            return hipGetLastError();
+        });
+    }
     // the transforms, and the pixels' running values between rounds
     const size_t lds = pair_lds_bytes(M, rows * G, (int)sizeof(R)) + (G < ppw ? (size_t)rows * M * sizeof(R) : 0);
     return by_side<R>(M, [&](auto ms) {

@@ -314,10 +314,10 @@ struct se2n_plan_s {
     // propagators + one flag byte per class (padded rows): class-major, or
     // element-major on the pair path
     size_t table_bytes() const {
-        return pair ? pair_table_bytes(M, N, (int)real_size()) : se2n::table_bytes(M, N, (int)real_size());
+        return pair ? pair_table_bytes(M, N, (int)real_size(), pg.lay.halved) : se2n::table_bytes(M, N, (int)real_size());
     }
     const uint8_t* flags_of(const void* P) const {
-        return pair ? (const uint8_t*)P + pair_table_entries(M, N) * real_size()
+        return pair ? (const uint8_t*)P + pair_table_entries(M, N, pg.lay.halved) * real_size()
                     : table_flags(P, M, N, (int)real_size());
     }
     // the propagator schedule runs on the pair path (se2n_pair.hpp): three
@@ -473,10 +473,10 @@ int get_propagators(se2n_plan p, double T, double beta, int n_steps, se2n_scheme
         ProfScope ps(p, "precompute", st);
         if (p->dt == SE2N_F32)
             e = launch_precompute<float>((float*)d, p->M, p->N, beta, T, n_steps, (int)scheme, st, p->keep_negligible,
-                                         p->pair);
+                                         p->pair + p->pg.lay.halved);
         else
             e = launch_precompute<double>((double*)d, p->M, p->N, beta, T, n_steps, (int)scheme, st,
-                                          p->keep_negligible, p->pair);
+                                          p->keep_negligible, p->pair + p->pg.lay.halved);
     }
     if (e != hipSuccess) {
         (void)hipFree(d);
@@ -807,7 +807,7 @@ int restore_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
                    "lift + row FFT");
     }
     for (int i = 0; i < n_int; ++i) {
-        if (p->pair) {
+        if (p->pair && !p->pg.lay.halved) {
             // a mesh point on whole rows of every pair in LDS
             if (i > 0 && dynamic)
                 SE2N_TIMED(p, "dr_step", st,
@@ -823,6 +823,7 @@ int restore_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
         }
         if (i > 0) {
             SE2N_TIMED(p, "row_inv_volume", st,
+                       p->pair ? launch_pair_inv<R>(PDST_VOLUME, w.spec, vol, p->M, p->N, p->pg, p->planM, tw, st) :
                        launch_row_inv<R>(DST_VOLUME, w.rows(), vol, nullptr, nullptr, p->M, p->N, p->N, R(1), p->geom,
                                          p->geom.inv_slices, p->planH, tw, st, true, w.blk != nullptr),
                        "inverse row FFT");
@@ -832,11 +833,13 @@ int restore_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
             else
                 SE2N_TIMED(p, "sr_mix", st, launch_sr_mix<R>(vol, f, mask, eps, p->M, p->N, st), "SR mix");
             SE2N_TIMED(p, "row_fwd", st,
+                       p->pair ? launch_pair_fwd<R>(PSRC_VOLUME, nullptr, nullptr, nullptr, vol, w.spec, p->M, p->N,
+                                                    p->pg, p->planM, tw, st) :
                        launch_row_fwd<R>(SRC_VOLUME, nullptr, nullptr, nullptr, vol, w.spec, p->M, p->N, p->geom,
                                          p->planH, tw, st),
                        "row FFT");
         }
-        rc = spectral_middle<R>(p, w.spec, w.blk, P, st);
+        rc = p->pair ? pair_middle<R>(p, w.spec, P, st) : spectral_middle<R>(p, w.spec, w.blk, P, st);
         if (rc) return rc;
     }
     rc = p->pair ? pair_project<R>(p, w.spec, mode, out, st)
@@ -933,7 +936,8 @@ int se2n_plan_create(se2n_plan* out, int M, int N, se2n_dtype dtype) {
         delete p;
         return rc;
     }
-    p->pair = pair_fits(M, N, (int)p->real_size()) && std::getenv("SE2N_NO_PAIR") == nullptr;
+    p->pair = (pair_fits(M, N, (int)p->real_size()) || pair_halves(M, N, (int)p->real_size())) &&
+              std::getenv("SE2N_NO_PAIR") == nullptr;
     if (p->pair) p->pg = pair_geom(M, N, (int)p->real_size(), num_cu);
     *out = p;
     return SE2N_OK;
