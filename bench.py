@@ -351,8 +351,9 @@ def bench_corrector(args) -> int:
         k = {}
         for name, (n, tot) in st.items():
             e = {"launches_per_step": n // args.steps, "ms_per_step": round(tot / args.steps, 5)}
-            if name in ("cnn_conv1", "cnn_conv2", "cnn_conv3", "cnn_dgrad", "cnn_wgrad"):
-                fl = flop_conv(M, B) * (n // args.steps)
+            if name in ("cnn_net", "cnn_net_loss", "cnn_dgrad", "cnn_wgrad"):
+                layers = 3 if name.startswith("cnn_net") else 1  # the three layers are one launch
+                fl = flop_conv(M, B) * layers * (n // args.steps)
                 e["TFLOP_s"] = round(fl / (tot / args.steps / 1e3) / 1e12, 1)
             k[name] = e
         res[mode] = {"M": M, "batch": B, "kernels": k,
@@ -394,7 +395,7 @@ def bench_corrector(args) -> int:
     }
     pit.close()
     print(f"[bench] iterated schedule at 1024^2: {iterated}", file=sys.stderr, flush=True)
-    dom = res["inference"]["kernels"]["cnn_conv2"]
+    dom = res["inference"]["kernels"]["cnn_net"]
     MFMA_BF16 = 2500.0
     line = {
         "metric": METRIC, "value": None, "unit": "voxel-steps/s", "n_gpus": 1, "steps": args.steps,
@@ -402,7 +403,7 @@ def bench_corrector(args) -> int:
         "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": "corrector: 3x3 conv N=32->32->32->N BF16 MFMA, inference 1024^2, training 16x256^2",
                    "N": N},
-        "roofline": {"kernel": "cnn_conv2 (inference)", "bound": "mfma", "achieved": dom["TFLOP_s"],
+        "roofline": {"kernel": "cnn_net (inference)", "bound": "mfma", "achieved": dom["TFLOP_s"],
                      "peak": MFMA_BF16, "unit": "TFLOP/s", "frac": round(dom["TFLOP_s"] / MFMA_BF16, 4),
                      "traffic": None},
         "corrector": res, "evaluation_1024": ev, "evaluation_256": ev256, "iterated_schedule_1024": iterated,

@@ -30,10 +30,8 @@ constexpr int kCnnL = kCnnW + kCnnC;            // parameters per layer
 constexpr int kCnnP = 3 * kCnnL;                // parameter vector length
 constexpr int kCnnTile = 16;                    // pixel tile side of the conv kernels
 constexpr int kCnnPart = kCnnW + kCnnC;         // one workgroup's weight + bias gradient partial
-constexpr int kCnnSlices = 64;                  // first-level sums of the partials
+constexpr int kCnnWgradParts = 512;             // weight gradient partials per layer at most
 constexpr int kCnnScaleBlocks = 512;            // partial sums of squares per image
-
-enum CnnEpi { CNN_HIDDEN = 0, CNN_LAST = 1, CNN_DGRAD = 2 };
 
 using bf16 = __bf16;
 
@@ -41,29 +39,30 @@ using bf16 = __bf16;
 hipError_t cnn_rms(const float* psi, float* parts, float* scale, int N, int M, int B, hipStream_t st);
 // psi planar FP32 [B][N][M][M] / scale[b] -> act bf16 channels-last [B][M][M][32] (zero channels >= N)
 hipError_t cnn_pack(const float* psi, const float* scale, bf16* act, int N, int M, int B, hipStream_t st);
-// One 3x3 conv 32 -> 32 over B images of side M (M % 16 == 0):
-//   HIDDEN: act_out = relu(conv(in) + bias)                        (bf16, channels last)
-//   LAST:   out[b][c] = coarse[b][c] + scale[b] (conv(in)[c] + bias[c]), c < N
-//           (FP32 planar; out may be coarse)
-//   DGRAD:  act_out = conv(in) * [mask > 0]                         (bf16, channels last; no bias)
-hipError_t cnn_conv(int epi, const bf16* in, const bf16* wA, const float* bias, bf16* act_out,
-                    const bf16* mask, const float* coarse, float* out, const float* scale, int N, int M, int B,
-                    hipStream_t st);
+// The network on B images of side M (M % 16 == 0):
+//   out = coarse + scale[b] (layer 3), channels < N   (FP32 planar)
+// a0: the packed input, needed when out overlaps coarse (which it may then
+// equal); nullptr: coarse / scale is packed on the way.
+hipError_t cnn_forward(const bf16* a0, const bf16* wf, const float* params, const float* coarse, float* out,
+                       const float* scale, int N, int M, int B, hipStream_t st);
+// The same for training: the packed input a0 and the activations a1, a2 of the
+// hidden layers (bf16, channels last) and, each image in units of scale[b],
+// d = (out - target) / scale[b] as g = gscale d (bf16 channels last, zero
+// channels >= N) and in sums of d^2 per tile (cnn_loss_blocks).
+hipError_t cnn_forward_loss(const bf16* wf, const float* params, const float* coarse, const float* target,
+                            const float* scale, bf16* a0, bf16* a1, bf16* a2, bf16* g, float* loss_parts, float gscale,
+                            int N, int M, int B, hipStream_t st);
+int cnn_loss_blocks(int M, int B);
+// Input gradient of a layer: out = conv(g) * [mask > 0]   (bf16, channels last)
+hipError_t cnn_dgrad(const bf16* g, const bf16* wd, const bf16* mask, bf16* out, int M, int B, hipStream_t st);
 // Weight + bias gradient partials of one layer: g (bf16 CL, the layer's output
 // gradient), a (bf16 CL, the layer's input); one partial of kCnnPart floats per
-// workgroup, each workgroup summing `tiles_per_wg` pixel tiles.
-int cnn_wgrad_parts(int M, int B, int tiles_per_wg);
-hipError_t cnn_wgrad(const bf16* g, const bf16* a, float* parts, int M, int B, int tiles_per_wg, hipStream_t st);
-// Sum the partials into the layer's slice of the gradient vector (W[o][c][tap], b[o]),
-// in a fixed order: kCnnSlices slice sums (scratch `slices`, kCnnSlices*kCnnPart
-// floats), then their sum.
-hipError_t cnn_wgrad_reduce(const float* parts, int nparts, float* slices, float* grad_layer, hipStream_t st);
-// Loss: out, target FP32 planar [B][N][M][M], each image in units of rms[b]:
-// d = (out - target)/rms[b]; g = scale*d to bf16 channels last (zero channels
-// >= N); per-block partial sums of d^2.
-int cnn_loss_blocks(int N, int M, int B);
-hipError_t cnn_loss(const float* out, const float* target, const float* rms, bf16* g, float* loss_parts, int N,
-                    int M, int B, float scale, hipStream_t st);
+// workgroup (cnn_wgrad_parts of them).
+int cnn_wgrad_parts(int M, int B);
+hipError_t cnn_wgrad(const bf16* g, const bf16* a, float* parts, int M, int B, hipStream_t st);
+// Sum the partials of the three layers (one after the other in parts) into the
+// gradient vector (per layer W[o][c][tap], b[o]), in a fixed order.
+hipError_t cnn_wgrad_reduce(const float* parts, int nparts, float* grads, hipStream_t st);
 // loss = sum(parts) * inv_numel (one value, deterministic order)
 hipError_t cnn_loss_reduce(const float* parts, int nparts, float inv_numel, float* loss, hipStream_t st);
 // Adam on the FP32 parameters (step t >= 1, bias-corrected), then refresh the MFMA weights.

@@ -48,8 +48,6 @@ struct se2n_cnn_s {
 
 namespace {
 
-constexpr int kTilesPerWg = 4;
-
 int check_cnn(se2n_cnn c) {
     if (!c) return fail(SE2N_EINVAL, "network is NULL");
     if (!c->alive) return fail(SE2N_ESTATE, "network was destroyed");
@@ -66,11 +64,11 @@ int check_shape(se2n_cnn c, int M, int B) {
 struct CnnWs {
     bf16 *a0, *a1, *a2, *g0, *g1;
     float *scale, *sparts;
-    float *out, *parts, *slices, *lparts;
+    float *parts, *lparts;
     size_t bytes;
 };
 
-CnnWs layout(const se2n_cnn c, int M, int B, bool training, char* base) {
+CnnWs layout(int M, int B, bool training, char* base) {
     CnnWs w{};
     size_t off = 0;
     const size_t act = align256((size_t)B * M * M * kCnnC * sizeof(bf16));
@@ -82,17 +80,13 @@ CnnWs layout(const se2n_cnn c, int M, int B, bool training, char* base) {
     w.scale = (float*)take((size_t)B * sizeof(float));
     w.sparts = (float*)take((size_t)B * kCnnScaleBlocks * sizeof(float));
     w.a0 = (bf16*)take(act);
-    w.a1 = (bf16*)take(act);
     if (training) {
+        w.a1 = (bf16*)take(act);
         w.a2 = (bf16*)take(act);
         w.g0 = (bf16*)take(act);
         w.g1 = (bf16*)take(act);
-        w.out = (float*)take((size_t)B * c->N * M * M * sizeof(float));
-        w.parts = (float*)take((size_t)cnn_wgrad_parts(M, B, kTilesPerWg) * kCnnPart * sizeof(float));
-        w.slices = (float*)take((size_t)kCnnSlices * kCnnPart * sizeof(float));
-        w.lparts = (float*)take((size_t)cnn_loss_blocks(c->N, M, B) * sizeof(float));
-    } else {
-        w.a2 = w.a0;  // the input is dead once layer 1 has run
+        w.parts = (float*)take((size_t)3 * cnn_wgrad_parts(M, B) * kCnnPart * sizeof(float));
+        w.lparts = (float*)take((size_t)cnn_loss_blocks(M, B) * sizeof(float));
     }
     w.bytes = off;
     return w;
@@ -129,63 +123,57 @@ int refresh_weights(se2n_cnn c, hipStream_t st) {
     return SE2N_OK;
 }
 
-// psi_out = psi + net(psi); `w` from layout(..., training)
+// out = psi + net(psi)
 int forward_impl(se2n_cnn c, const float* psi, float* out, int M, int B, const CnnWs& w, hipStream_t st) {
-    const int N = c->N;
-    CNN_TIMED(c, "cnn_rms", st, cnn_rms(psi, w.sparts, w.scale, N, M, B, st), "corrector input scale");
-    CNN_TIMED(c, "cnn_pack", st, cnn_pack(psi, w.scale, w.a0, N, M, B, st), "corrector input packing");
-    CNN_TIMED(c, "cnn_conv1", st,
-              cnn_conv(CNN_HIDDEN, w.a0, c->wf, c->params + kCnnW, w.a1, nullptr, nullptr, nullptr, nullptr, N, M, B,
-                       st),
-              "corrector layer 1");
-    CNN_TIMED(c, "cnn_conv2", st,
-              cnn_conv(CNN_HIDDEN, w.a1, c->wf + kCnnW, c->params + kCnnL + kCnnW, w.a2, nullptr, nullptr, nullptr,
-                       nullptr, N, M, B, st),
-              "corrector layer 2");
-    CNN_TIMED(c, "cnn_conv3", st,
-              cnn_conv(CNN_LAST, w.a2, c->wf + 2 * kCnnW, c->params + 2 * kCnnL + kCnnW, nullptr, nullptr, psi, out,
-                       w.scale, N, M, B, st),
-              "corrector layer 3");
+    CNN_TIMED(c, "cnn_rms", st, cnn_rms(psi, w.sparts, w.scale, c->N, M, B, st), "corrector input scale");
+    // in place, a tile's halo has to come from a copy
+    const size_t n = (size_t)B * c->N * M * M;
+    const bool overlap = out < psi + n && psi < out + n;
+    if (overlap) CNN_TIMED(c, "cnn_pack", st, cnn_pack(psi, w.scale, w.a0, c->N, M, B, st), "corrector input packing");
+    CNN_TIMED(c, "cnn_net", st,
+              cnn_forward(overlap ? w.a0 : nullptr, c->wf, c->params, psi, out, w.scale, c->N, M, B, st),
+              "corrector layers");
     return SE2N_OK;
 }
 
-int layer_wgrad(se2n_cnn c, const bf16* g, const bf16* a, float* grad_layer, int M, int B, const CnnWs& w,
-                hipStream_t st) {
-    const int nparts = cnn_wgrad_parts(M, B, kTilesPerWg);
-    CNN_TIMED(c, "cnn_wgrad", st, cnn_wgrad(g, a, w.parts, M, B, kTilesPerWg, st), "corrector weight gradient");
-    CNN_TIMED(c, "cnn_wgrad_reduce", st, cnn_wgrad_reduce(w.parts, nparts, w.slices, grad_layer, st),
-              "corrector gradient reduction");
+// The weight gradient's partials of layer l
+int layer_wgrad(se2n_cnn c, int l, const bf16* g, const bf16* a, int M, int B, const CnnWs& w, hipStream_t st) {
+    float* parts = w.parts + (size_t)l * cnn_wgrad_parts(M, B) * kCnnPart;
+    CNN_TIMED(c, "cnn_wgrad", st, cnn_wgrad(g, a, parts, M, B, st), "corrector weight gradient");
     return SE2N_OK;
 }
 
 int gradients_impl(se2n_cnn c, const float* coarse, const float* fine, int M, int B, float* grads, float* loss,
                    const CnnWs& w, hipStream_t st) {
-    int rc = forward_impl(c, coarse, w.out, M, B, w, st);
-    if (rc) return rc;
-    const int N = c->N;
-    const double numel = (double)B * N * M * M;
-    const int nl = cnn_loss_blocks(N, M, B);
-    CNN_TIMED(c, "cnn_loss", st,
-              cnn_loss(w.out, fine, w.scale, w.g0, w.lparts, N, M, B, (float)(2.0 / numel), st), "corrector loss");
+    CNN_TIMED(c, "cnn_rms", st, cnn_rms(coarse, w.sparts, w.scale, c->N, M, B, st), "corrector input scale");
+    const double numel = (double)B * c->N * M * M;
+    const int nl = cnn_loss_blocks(M, B);
+    CNN_TIMED(c, "cnn_net_loss", st,
+              cnn_forward_loss(c->wf, c->params, coarse, fine, w.scale, w.a0, w.a1, w.a2, w.g0, w.lparts,
+                               (float)(2.0 / numel), c->N, M, B, st),
+              "corrector layers and loss");
     if (loss) {
         CNN_TIMED(c, "cnn_loss_reduce", st, cnn_loss_reduce(w.lparts, nl, (float)(1.0 / numel), loss, st),
                   "corrector loss reduction");
     }
     // layer 3: g0 = dloss/dr
-    rc = layer_wgrad(c, w.g0, w.a2, grads + 2 * kCnnL, M, B, w, st);
+    int rc = layer_wgrad(c, 2, w.g0, w.a2, M, B, w, st);
     if (rc) return rc;
     CNN_TIMED(c, "cnn_dgrad", st,
-              cnn_conv(CNN_DGRAD, w.g0, c->wd + 2 * kCnnW, nullptr, w.g1, w.a2, nullptr, nullptr, nullptr, N, M, B,
-                       st),
+              cnn_dgrad(w.g0, c->wd + 2 * kCnnW, w.a2, w.g1, M, B, st),
               "corrector input gradient (layer 3)");
     // layer 2: g1 = dloss/dz2
-    rc = layer_wgrad(c, w.g1, w.a1, grads + kCnnL, M, B, w, st);
+    rc = layer_wgrad(c, 1, w.g1, w.a1, M, B, w, st);
     if (rc) return rc;
     CNN_TIMED(c, "cnn_dgrad", st,
-              cnn_conv(CNN_DGRAD, w.g1, c->wd + kCnnW, nullptr, w.g0, w.a1, nullptr, nullptr, nullptr, N, M, B, st),
+              cnn_dgrad(w.g1, c->wd + kCnnW, w.a1, w.g0, M, B, st),
               "corrector input gradient (layer 2)");
     // layer 1: g0 = dloss/dz1
-    return layer_wgrad(c, w.g0, w.a0, grads, M, B, w, st);
+    rc = layer_wgrad(c, 0, w.g0, w.a0, M, B, w, st);
+    if (rc) return rc;
+    CNN_TIMED(c, "cnn_wgrad_reduce", st, cnn_wgrad_reduce(w.parts, cnn_wgrad_parts(M, B), grads, st),
+              "corrector gradient reduction");
+    return SE2N_OK;
 }
 
 int adam_impl(se2n_cnn c, const float* grads, float lr, float b1, float b2, float eps, hipStream_t st) {
@@ -362,7 +350,7 @@ int se2n_cnn_set_adam(se2n_cnn c, const float* m, const float* v, int count, int
 size_t se2n_cnn_workspace_bytes(se2n_cnn c, int M, int batch, int training) {
     clear_error();
     if (check_cnn(c) || check_shape(c, M, batch)) return 0;
-    return layout(c, M, batch, training != 0, nullptr).bytes;
+    return layout(M, batch, training != 0, nullptr).bytes;
 }
 
 int se2n_cnn_forward(se2n_cnn c, const float* psi, float* out, int M, int batch, void* workspace, void* stream) {
@@ -371,7 +359,7 @@ int se2n_cnn_forward(se2n_cnn c, const float* psi, float* out, int M, int batch,
     if (!rc) rc = check_shape(c, M, batch);
     if (rc) return rc;
     if (!psi || !out || !workspace) return fail(SE2N_EINVAL, "psi, out and workspace must be non-NULL");
-    const CnnWs w = layout(c, M, batch, false, (char*)workspace);
+    const CnnWs w = layout(M, batch, false, (char*)workspace);
     return forward_impl(c, psi, out, M, batch, w, (hipStream_t)stream);
 }
 
@@ -383,7 +371,7 @@ int se2n_cnn_gradients(se2n_cnn c, const float* coarse, const float* fine, int M
     if (rc) return rc;
     if (!coarse || !fine || !grads || !workspace)
         return fail(SE2N_EINVAL, "coarse, fine, grads and workspace must be non-NULL");
-    const CnnWs w = layout(c, M, batch, true, (char*)workspace);
+    const CnnWs w = layout(M, batch, true, (char*)workspace);
     return gradients_impl(c, coarse, fine, M, batch, grads, loss, w, (hipStream_t)stream);
 }
 
@@ -402,7 +390,7 @@ int se2n_cnn_train_step(se2n_cnn c, const float* coarse, const float* fine, int 
     if (!rc) rc = check_shape(c, M, batch);
     if (rc) return rc;
     if (!coarse || !fine || !workspace) return fail(SE2N_EINVAL, "coarse, fine and workspace must be non-NULL");
-    const CnnWs w = layout(c, M, batch, true, (char*)workspace);
+    const CnnWs w = layout(M, batch, true, (char*)workspace);
     rc = gradients_impl(c, coarse, fine, M, batch, c->grads, loss ? loss : c->loss, w, (hipStream_t)stream);
     if (rc) return rc;
     return adam_impl(c, c->grads, lr, 0.9f, 0.999f, 1e-8f, (hipStream_t)stream);
@@ -535,7 +523,7 @@ int se2n_inpaint_corrected(se2n_plan plan, se2n_cnn c, const void* f, const uint
     if (!rc) rc = se2n_lift(plan, f, mask, rmap_out, psi, stream);
     if (!rc) rc = se2n_diffuse(plan, psi, T, beta, n_steps, scheme, pws, stream);
     if (rc) return rc;
-    const CnnWs w = layout(c, M, 1, false, cws);
+    const CnnWs w = layout(M, 1, false, cws);
     rc = forward_impl(c, psi, psi, M, 1, w, st);
     if (rc) return rc;
     return se2n_project(plan, psi, mode, out, stream);
