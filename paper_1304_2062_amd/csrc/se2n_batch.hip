@@ -162,11 +162,11 @@ __global__ __launch_bounds__(BT) void kb_col_orient(const BItem* __restrict__ it
 // Orientation stencil over the tiles of images that share (M, sigma), hence
 // the taps.
 template <int RAD>
-__global__ __launch_bounds__(kOrientNT) void kb_orient_stencil(const BItem* __restrict__ items,
+__global__ __launch_bounds__(OrientLarge::NT) void kb_orient_stencil(const BItem* __restrict__ items,
                                                                const int4* __restrict__ tiles, int ntiles,
                                                                OrientTaps taps) {
-    __shared__ float sa[orient_lds_floats<RAD>()];
-    __shared__ float sb[orient_lds_floats<RAD>()];
+    __shared__ float sa[OrientLarge::lds_floats(RAD)];
+    __shared__ float sb[OrientLarge::lds_floats(RAD)];
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int4 tl = tiles[t];
         const BItem& d = item_of(items, tl.x);
@@ -302,12 +302,12 @@ hipError_t with_kernel(int kind, int N, int cls, F&& f) {
         }
         case BK_ORIENT_STENCIL:
             switch (cls) {
-                case 8: return f((const void*)kb_orient_stencil<8>, kOrientNT);
-                case 12: return f((const void*)kb_orient_stencil<12>, kOrientNT);
-                case 16: return f((const void*)kb_orient_stencil<16>, kOrientNT);
-                case 20: return f((const void*)kb_orient_stencil<20>, kOrientNT);
-                case 24: return f((const void*)kb_orient_stencil<24>, kOrientNT);
-                case 32: return f((const void*)kb_orient_stencil<32>, kOrientNT);
+                case 8: return f((const void*)kb_orient_stencil<8>, OrientLarge::NT);
+                case 12: return f((const void*)kb_orient_stencil<12>, OrientLarge::NT);
+                case 16: return f((const void*)kb_orient_stencil<16>, OrientLarge::NT);
+                case 20: return f((const void*)kb_orient_stencil<20>, OrientLarge::NT);
+                case 24: return f((const void*)kb_orient_stencil<24>, OrientLarge::NT);
+                case 32: return f((const void*)kb_orient_stencil<32>, OrientLarge::NT);
                 default: return hipErrorInvalidValue;
             }
         case BK_FILL: return f((const void*)kb_enc<false>, BT);

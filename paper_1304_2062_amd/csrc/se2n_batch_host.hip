@@ -190,7 +190,7 @@ std::vector<Tile> raw_tiles(const std::vector<Shape>& sh, const se2n_tune& t, in
                 const int rad = orient_stencil_taps_cached(M, x.sigma, nullptr);
                 if (rad == 0) break;
                 for (int tt = 0; tt < orient_tiles(M); ++tt)
-                    out.push_back({make_int4(i, tt, rad, 0), (double)kOrientTX * kOrientTY * (2 * rad + 1)});
+                    out.push_back({make_int4(i, tt, rad, 0), (double)OrientLarge::TX * OrientLarge::TY * (2 * rad + 1)});
                 break;
             }
             case 3:
