@@ -67,10 +67,16 @@ __host__ __device__ constexpr int pair_max_threads(int rsize) { return rsize == 
 
 // Middle pass: elements per thread, and threads: M/4 class positions times
 // the row groups of the per-mode product (ept / 4 rows of the four modes of a
-// class, see pair_solve).
-__host__ __device__ constexpr int pair_mid_ept(int elems) { return elems <= 1024 ? 4 : elems <= 4096 ? 8 : 16; }
-__host__ __device__ constexpr int pair_mid_threads(int M, int hs) {
-    const int rpt = pair_mid_ept(hs * M) / 4;
+// class, see pair_solve).  8 elements, and twice the threads, up to 5120
+// elements in FP32 (324^2, N = 15 32.5 -> 26.3 us, 768^2, N = 12 28.0 -> 25.2
+// us; 6144 elements 768^2, N = 16 32.4 -> 34.9 us; a side of 1024, which takes
+// three stages with 16 and four with 8, N = 10 30.7 -> 33.4 us).
+__host__ __device__ constexpr int pair_mid_ept(int M, int hs, int rsize) {
+    const int elems = hs * M;
+    return elems <= 1024 ? 4 : elems <= (rsize == 4 && M < 1024 ? 5120 : 4096) ? 8 : 16;
+}
+__host__ __device__ constexpr int pair_mid_threads(int M, int hs, int rsize) {
+    const int rpt = pair_mid_ept(M, hs, rsize) / 4;
     return (M / 4 * ((hs + rpt - 1) / rpt) + 63) / 64 * 64;
 }
 
@@ -98,7 +104,7 @@ __host__ __device__ constexpr size_t pair_table_bytes(int M, int N, int rsize, b
 // column fits in the LDS of one workgroup, at most 16 elements per thread.
 __host__ __device__ constexpr bool pair_block_fits(int M, int N, int rsize) {
     const int hs = pair_hs(N);
-    return hs * M <= 16 * pair_max_threads(rsize) && pair_mid_threads(M, hs) <= pair_max_threads(rsize) &&
+    return hs * M <= 16 * pair_max_threads(rsize) && pair_mid_threads(M, hs, rsize) <= pair_max_threads(rsize) &&
            pair_lds_bytes(M, hs, rsize) <= (size_t)kPairLds;
 }
 __host__ __device__ constexpr bool pair_fits(int M, int N, int rsize) {
@@ -1239,8 +1245,8 @@ inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
         g.inv_ept = g.fwd_ept;
         g.inv_threads = pair_threads(g.inv_rows * M, g.inv_ept);
         const int hs = pair_hs(N);
-        g.mid_ept = pair_mid_ept(hs * M / 2);
-        g.mid_threads = pair_mid_threads(M / 2, hs);
+        g.mid_ept = pair_mid_ept(M / 2, hs, rsize);
+        g.mid_threads = pair_mid_threads(M / 2, hs, rsize);
         g.mid_grid = M * pair_nblk(N);
         if (2 * pair_lds_bytes(M / 2, hs, rsize) > (size_t)kPairLds && g.mid_grid > num_cu) g.mid_grid = num_cu;
         return g;
@@ -1262,8 +1268,8 @@ inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     g.inv_ept = r * G * M <= 8 * most ? 8 : 16;
     g.inv_threads = pair_threads(r * G * M, g.inv_ept);
     const int hs = pair_hs(N);
-    g.mid_ept = pair_mid_ept(hs * M);
-    g.mid_threads = pair_mid_threads(M, hs);
+    g.mid_ept = pair_mid_ept(M, hs, rsize);
+    g.mid_threads = pair_mid_threads(M, hs, rsize);
     g.mid_grid = M / 2 * pair_nblk(N);
     if (2 * pair_lds_bytes(M, hs, rsize) > (size_t)kPairLds && g.mid_grid > num_cu) g.mid_grid = num_cu;
     // one row of every pair is no larger than a column block of the middle pass
