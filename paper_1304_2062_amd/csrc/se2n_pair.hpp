@@ -894,8 +894,10 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
                 }
             }
         }
-        for (int t = t_begin; t < t_end; ++t) {
-            C2<R> v[MAXB][R0];
+        C2<R> v[MAXB][R0];
+        // stage-0 inputs of pair t; a volume's are fetched one pair ahead,
+        // behind the transform of the pair before
+        auto inputs = [&](int t) {
 #pragma unroll
             for (int i = 0; i < MAXB; ++i) {
                 const int b = tid + i * nthr;
@@ -904,9 +906,14 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
                     const int j = b - row * NB;
 #pragma unroll
                     for (int r = 0; r < R0; ++r)
-                        v[i][r] = SRC == PSRC_LIFT ? lifted(t, (int)((rv[i][r / 4] >> (8 * (r % 4))) & 0xff), fv[i][r]) : from_volume(t, row, j + r * NB);
+                        v[i][r] = SRC == PSRC_LIFT ? lifted(t, (int)((rv[i][r / 4] >> (8 * (r % 4))) & 0xff), fv[i][r])
+                                                   : from_volume(t, row, j + r * NB);
                 }
             }
+        };
+        if constexpr (SRC == PSRC_VOLUME) inputs(t_begin);
+        for (int t = t_begin; t < t_end; ++t) {
+            if constexpr (SRC == PSRC_LIFT) inputs(t);
 #pragma unroll
             for (int i = 0; i < MAXB; ++i) {
                 const int b = tid + i * nthr;
@@ -926,6 +933,8 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
                 }
             }
             __syncthreads();
+            if constexpr (SRC == PSRC_VOLUME)
+                if (t + 1 < t_end) inputs(t + 1);
             pair_fft_from<R, false, MS, EPT, 1, R0>(buf, tw, rows, tid, nthr, PairLds{}, PairLds{});
             if constexpr (HALF) pair_unpack_half<R, MS>(buf, spec, lay, N, t, rows, y0, tw, tid, nthr);
             else pair_unpack<R, MS>(buf, spec, lay, M, N, t, 0, rows, y0, tid, nthr);
