@@ -298,9 +298,11 @@ int se2n_profile_stats(se2n_plan plan, se2n_kernel_stat *out, int capacity, int 
  * max or mean projection) for `count` images of possibly different M, N,
  * T, beta, n_steps, sigma.  Each pass (orientation rows / columns /
  * inverse rows, lift + row FFT, column FFT, per-mode propagation, inverse
- * column FFT, inverse row FFT + projection) is ONE persistent launch over
- * the tiles of every image; the passes of a batch are captured once into a
- * hipGraph that each call replays with a single graph launch.
+ * column FFT, inverse row FFT + projection) is one launch over the tiles of
+ * the images that take it.  Images of sides 128, 192, 256, 384, 512, 768 and
+ * 1024 whose column blocks fit in LDS go through three passes instead, in
+ * groups of one side and N.  All of a batch is captured once into a hipGraph
+ * that each call replays with a single graph launch.
  *
  * The library keeps, per device and per batch signature (the list of
  * (M, N, n_steps, scheme, proj, T, beta, sigma) of the items, pointers
@@ -334,7 +336,8 @@ typedef struct {
 
 /* Schedule of a batch (what the autotuner chooses).
  *   wg_per_cu   persistent workgroups per compute unit for every pass
- *               (1..16); 0 launches one workgroup per tile instead.
+ *               (1..16); 0 launches one workgroup per tile instead, as the
+ *               three-pass groups always do.
  *   order       0: tiles of each pass sorted by decreasing cost (largest
  *               first), 1: image by image in item order.
  *   row_groups  slice groups of the lift and inverse row passes (1..64,
@@ -389,7 +392,7 @@ int se2n_batch_set_tune(const se2n_item *items, int count, const se2n_tune *tune
 int se2n_batch_get_tune(const se2n_item *items, int count, se2n_tune *out);
 
 /* The tile list of one pass of a batch under `tune` (NULL: the current
- * schedule), in execution order, 4 ints per tile {item, a, b, c}:
+ * schedule) with every image on the five passes, in execution order, 4 ints per tile {item, a, b, c}:
  *   pass 0 orientation rows     {item, row block, 0, 1}
  *   pass 1 orientation columns  {item, first column kx, 0, 0}
  *   pass 2 orientation inverse  {item, row block, 0, 2}
