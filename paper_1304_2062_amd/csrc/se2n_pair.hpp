@@ -112,11 +112,12 @@ __host__ __device__ constexpr bool pair_fits(int M, int N, int rsize) {
 }
 // Or half a column does: the row passes take the columns' first radix-2 step
 // (PairLay).  FP64 on the sides with compiled transforms, 1024^2, N = 32 751
-// -> 478 us against the five passes, 512^2, N = 40 308 -> 184 us, 2048^2,
-// N = 16 1500 -> 1010 us.  Not FP32: its five passes run at the memory's rate
+// -> 478 us against the five passes, 512^2, N = 40 308 -> 184 us, 768^2,
+// N = 30 439 -> 303 us, 384^2, N = 44 212 -> 154 us, 2048^2, N = 16 1500 ->
+// 1010 us.  Not FP32: its five passes run at the memory's rate
 // (1024^2, N = 48 381 against 450 us this way, 2048^2, N = 32 755 against 1080).
 __host__ __device__ constexpr bool pair_halves(int M, int N, int rsize) {
-    return rsize == 8 && (M == 512 || M == 1024 || M == 2048) && !pair_fits(M, N, rsize) &&
+    return rsize == 8 && (M == 384 || M == 512 || M == 768 || M == 1024 || M == 2048) && !pair_fits(M, N, rsize) &&
            pair_block_fits(M / 2, N, rsize);
 }
 

@@ -160,7 +160,9 @@ hipError_t launch_pair_mid(C2<R>* spec, const R* T, int M, int N, const PairGeom
                            const C2<R>* tw, hipStream_t st) {
     if constexpr (sizeof(R) == 8) {
         if (g.lay.halved) {
+            if (M == 384) return mid_half<R, 192>(spec, T, N, g, tw, st);
             if (M == 512) return mid_half<R, 256>(spec, T, N, g, tw, st);
+            if (M == 768) return mid_half<R, 384>(spec, T, N, g, tw, st);
             if (M == 1024) return mid_half<R, 512>(spec, T, N, g, tw, st);
             return mid_half<R, 1024>(spec, T, N, g, tw, st);
         }

@@ -102,7 +102,9 @@ hipError_t by_side(int M, F&& f) {
 // The sides whose columns may be halved (pair_halves).
 template <class F>
 hipError_t by_half_side(int M, F&& f) {
+    if (M == 384) return f(std::integral_constant<int, 384>{});
     if (M == 512) return f(std::integral_constant<int, 512>{});
+    if (M == 768) return f(std::integral_constant<int, 768>{});
     if (M == 1024) return f(std::integral_constant<int, 1024>{});
     return f(std::integral_constant<int, 2048>{});
 }

@@ -41,6 +41,12 @@ def _rel(a, b):
 
 
 CASES = [
+    (384, 23, F64, "cn", "max"),
+    (384, 44, F64, "exact", "max"),
+    (384, 64, F64, "cn", "mean"),
+    (768, 21, F64, "cn", "mean"),
+    (768, 22, F64, "cn", "max"),
+    (768, 42, F64, "cn", "max"),
     (512, 34, F64, "cn", "max"),
     (512, 64, F64, "exact", "mean"),
     (512, 31, F64, "cn", "max"),
@@ -73,7 +79,7 @@ def test_halved_columns_equal_the_five_passes(monkeypatch, M, N, dtype, scheme, 
     assert _rel(pair.project(a, proj), got) < _tol(M)
 
 
-@pytest.mark.parametrize("M,N,dtype,dynamic", [(512, 34, F64, False), (512, 34, F64, True), (1024, 15, F64, True),
+@pytest.mark.parametrize("M,N,dtype,dynamic", [(384, 44, F64, True), (768, 24, F64, False), (512, 34, F64, False), (512, 34, F64, True), (1024, 15, F64, True),
                                                (2048, 4, F64, False)])
 def test_restoration_with_halved_columns(monkeypatch, M, N, dtype, dynamic):
     print(f"halves restore {M} {N} {dtype} dynamic={dynamic}", flush=True)
