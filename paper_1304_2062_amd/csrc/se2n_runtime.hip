@@ -502,20 +502,29 @@ const void* find_propagators(se2n_plan p, double T, double beta, int n_steps, se
     return nullptr;
 }
 
-// Estimated milliseconds of the two CN schedules on MI355X, from measured
-// per-unit costs: the iterated kernel per mode and step, the FP64 propagator
-// build per class (on the matrix cores, one 16 x 16 tile or four per block)
-// and per product of the binary powering.  Used only to choose a schedule
-// for an uncached key.
-// (FP32: 2048^2, N = 32, 6.66 ms for 400 iterated steps; builds of 1024^2, N = 32,
-// 200 steps 0.22 ms and of 384^2, N = 64, 100 steps 0.18 ms.)
+// Estimated milliseconds of the two CN schedules on MI355X: the iterated kernel
+// per mode and step, the FP64 propagator build per stored class and per product
+// of the binary powering (200 steps are 10.6 / 11.6 of the unit).  Used only to
+// choose a schedule for an uncached key.
+//
+// Measured at 1024^2, FP32, builds of 200 steps: N = 4 121 us, N = 16 134 us, N = 32
+// 226 us, N = 64 841 us; iterated 0.55, 2.3, 4.6 and 13 us a step.  What an iterated
+// call gives up counts too: the three passes where the plan has them, the exactness
+// of the table (FP32 steps round n times) and the table itself, which the key's next
+// call builds anyway.  So up to N = 16 a build is taken for less than it costs, by
+// the growth of its products, (h / 16)^3: at 1024^2 that gives N = 4 the table from
+// 2 steps on (first call at 10 steps 162 us against 116 iterated, the next 73
+// against 115; at 50 steps of N = 8 228 against 191, then 86 against 188), N = 8 from
+// 9 and N = 16 from 49 (at 50 steps 313 us against 281, then 131 against 282).
 double est_iterated_ms(int M, int N, int n) {
     return 8.0e-9 * (double)(M / 2 + 1) * M * n * (N / 32.0);
 }
 double est_precompute_ms(int M, int N, int n) {
+    const double h = N / 2.0;                          // even N only (use_iterated)
     const double classes = (double)table_slots(M, N);  // one build per stored class
     const double products = (std::log2((double)n) + 3.0) / 11.6;
-    return (N <= 32 ? 7.0e-6 : 4.5e-5) * classes * products;
+    const double unit = h <= 8 ? 3.3e-5 * (h * h * h / 4096.0) : h <= 16 ? 1.0e-5 : 2.8e-5;
+    return unit * classes * products;
 }
 
 // Whether this CN diffusion runs the iterated schedule.  AUTO: a cached
