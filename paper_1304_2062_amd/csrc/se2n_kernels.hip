@@ -467,6 +467,39 @@ struct RegMat {
     }
 };
 
+// Out of the accumulators.  A v_mfma_f64_16x16x4 (16 passes) may be read 19 wait
+// states after its issue.  Left to itself the compiler puts that wait in front of
+// the first read, and where a loop's branch lies between the two it counted too
+// little: in the squaring loop of the powering, on the way round that skips the
+// multiplication, it read the last register 6 states after the MFMA that writes
+// it (element 3 came back stale from the second squaring on).  So the wait stands
+// here, on the accumulators themselves, and so do the reads, which the compiler
+// would otherwise give a wait of their own; the last two states are those that an
+// MFMA needs after a vector instruction has written its operand.
+template <int TILES>
+__device__ __forceinline__ void accumulators_out(RegMat<TILES>& D) {
+    typedef int i32x8 __attribute__((ext_vector_type(8)));
+    if constexpr (TILES == 1)
+        asm volatile("s_nop 15\n\ts_nop 2" : "+a"(D.t[0][0]));
+    else
+        asm volatile("s_nop 15\n\ts_nop 2"
+                     : "+a"(D.t[0][0]), "+a"(D.t[0][1]), "+a"(D.t[1][0]), "+a"(D.t[1][1]));
+#pragma unroll
+    for (int a = 0; a < TILES; ++a)
+#pragma unroll
+        for (int b = 0; b < TILES; ++b) {
+            const i32x8 x = __builtin_bit_cast(i32x8, D.t[a][b]);
+            int y0, y1, y2, y3, y4, y5, y6, y7;
+            asm volatile("v_accvgpr_read_b32 %0, %8\n\tv_accvgpr_read_b32 %1, %9\n\t"
+                         "v_accvgpr_read_b32 %2, %10\n\tv_accvgpr_read_b32 %3, %11\n\t"
+                         "v_accvgpr_read_b32 %4, %12\n\tv_accvgpr_read_b32 %5, %13\n\t"
+                         "v_accvgpr_read_b32 %6, %14\n\tv_accvgpr_read_b32 %7, %15\n\ts_nop 1"
+                         : "=&v"(y0), "=&v"(y1), "=&v"(y2), "=&v"(y3), "=&v"(y4), "=&v"(y5), "=&v"(y6), "=&v"(y7)
+                         : "a"(x[0]), "a"(x[1]), "a"(x[2]), "a"(x[3]), "a"(x[4]), "a"(x[5]), "a"(x[6]), "a"(x[7]));
+            D.t[a][b] = __builtin_bit_cast(mf64x4, i32x8{y0, y1, y2, y3, y4, y5, y6, y7});
+        }
+}
+
 // D = X Y, X symmetric.
 template <int TILES>
 __device__ __forceinline__ RegMat<TILES> reg_mul(const RegMat<TILES>& X, const RegMat<TILES>& Y) {
@@ -481,20 +514,7 @@ __device__ __forceinline__ RegMat<TILES> reg_mul(const RegMat<TILES>& X, const R
 #pragma unroll
                 for (int b = 0; b < TILES; ++b)
                     D.t[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(X.t[c][a][kk], Y.t[c][b][kk], D.t[a][b], 0, 0, 0);
-    // take the results out of the accumulators here: where a loop's branch lay
-    // between the last MFMA and the first read of its result, the compiled
-    // code waited too short (element 3 came back stale from the second
-    // squaring on); within one block the wait is right
-#pragma unroll
-    for (int a = 0; a < TILES; ++a)
-#pragma unroll
-        for (int b = 0; b < TILES; ++b)
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                double x = D.t[a][b][kk];
-                asm volatile("" : "+v"(x));
-                D.t[a][b][kk] = x;
-            }
+    accumulators_out<TILES>(D);
     return D;
 }
 
