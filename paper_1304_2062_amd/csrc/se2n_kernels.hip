@@ -444,8 +444,8 @@ __global__ __launch_bounds__(64) void k_precompute(R* __restrict__ Ptab, int M, 
 // registers, with no LDS and no barrier in the powering.  Bound by the chain
 // of dependent products of each wavefront (FP32 tables, against operands
 // through LDS for blocks of 9..16 and scalar products for the others):
-// 1024^2, N = 32, 200 steps 278 -> 216 us, 384^2, N = 48, 100 steps 900 -> 145,
-// N = 64 3276 -> 180, 256^2, N = 31, 200 steps 1325 -> 98.  Rounding leaves
+// 1024^2, N = 32, 200 steps 278 -> 200 us, 384^2, N = 48, 100 steps 900 -> 152,
+// N = 64 3276 -> 185, 256^2, N = 31, 200 steps 1325 -> 108.  Rounding leaves
 // R = C^n asymmetric by a few ulps; the stored entries are symmetrised.
 //   CN:    the left matrix I - tau A / 2 is cyclic tridiagonal: one lane per
 //          block factors it (Thomas elimination with a Sherman-Morrison
@@ -1077,9 +1077,15 @@ hipError_t launch_precompute(R* Ptab, int M, int N, double beta, double T, int n
     const size_t lds = (size_t)(4 * h * h + h) * sizeof(double);
     // the inverse FFT's 1/M^2, and for even N the 1/2 of the p/q recombination
     const double scale = ((N & 1) ? 1.0 : 0.5) / ((double)M * (double)M);
-    // matrix cores for blocks of at most 32; SE2N_SCALAR_PRECOMPUTE forces the
-    // scalar build, which odd N above 32 keeps
-    if (h <= 32 && std::getenv("SE2N_SCALAR_PRECOMPUTE") == nullptr) {
+    // Matrix cores for blocks of at most 32, except where many classes of the
+    // smallest blocks, padded to 16, make the products the bound: 200 steps of
+    // N = 4 / 6 / 8 / 10, matrix cores against scalar, 256^2 19.3 / 27.9 / 21.0 / 29.5
+    // against 19.7 / 26.0 / 23.7 / 31.9 us, 384^2 28.5 / 48.6 / 30.2 / 50.7 against 25.2 /
+    // 42.2 / 30.3 / 50.7, 1024^2 138 / 261 / 143 / 275 against 107 / 211 / 128 / 257; N = 5 as
+    // N = 6; N = 7 and 9 (one block of N) 193 and 201 against 203 and 323 at 1024^2.
+    // SE2N_SCALAR_PRECOMPUTE forces the scalar build, which odd N above 32 keeps.
+    const bool small = N <= 6 ? M >= 384 : !(N & 1) && N <= 10 && M >= 768;
+    if (h <= 32 && !small && std::getenv("SE2N_SCALAR_PRECOMPUTE") == nullptr) {
         if (h <= 16)
             hipLaunchKernelGGL((k_precompute_mfma<R, 1>), dim3((unsigned)slots), dim3(64), 0, st, Ptab, M, N, Q,
                                flag_stride(M), beta, T, nsteps, scheme, scale, keep_all ? 1 : 0, pair);

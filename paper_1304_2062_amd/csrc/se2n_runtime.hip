@@ -507,8 +507,8 @@ const void* find_propagators(se2n_plan p, double T, double beta, int n_steps, se
 // of the binary powering (200 steps are 10.6 / 11.6 of the unit).  Used only to
 // choose a schedule for an uncached key.
 //
-// Measured at 1024^2, FP32, builds of 200 steps: N = 4 121 us, N = 16 134 us, N = 32
-// 226 us, N = 64 841 us; iterated 0.55, 2.3, 4.6 and 13 us a step.  What an iterated
+// Measured at 1024^2, FP32, builds of 200 steps: N = 4 107 us, N = 16 155 us, N = 32
+// 200 us, N = 64 958 us; iterated 0.55, 2.3, 4.6 and 13 us a step.  What an iterated
 // call gives up counts too: the three passes where the plan has them, the exactness
 // of the table (FP32 steps round n times) and the table itself, which the key's next
 // call builds anyway.  So up to N = 16 a build is taken for less than it costs, by
@@ -523,7 +523,7 @@ double est_precompute_ms(int M, int N, int n) {
     const double h = N / 2.0;                          // even N only (use_iterated)
     const double classes = (double)table_slots(M, N);  // one build per stored class
     const double products = (std::log2((double)n) + 3.0) / 11.6;
-    const double unit = h <= 8 ? 3.3e-5 * (h * h * h / 4096.0) : h <= 16 ? 1.0e-5 : 2.8e-5;
+    const double unit = h <= 8 ? 3.3e-5 * (h * h * h / 4096.0) : h <= 16 ? 1.0e-5 : 3.0e-5;
     return unit * classes * products;
 }
 
