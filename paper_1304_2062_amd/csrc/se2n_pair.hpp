@@ -1195,7 +1195,17 @@ struct PairGeom {
     int inv_rows, inv_G, inv_threads, inv_ept;      // projecting inverse rows: all pairs, G at a time
     int mid_threads, mid_ept, mid_grid;             // middle pass; column blocks, or walkers
     int all_threads, all_ept;                       // one row of all pairs (restoration)
+    bool whole_sr, whole_dr;                        // a mesh point of a restoration runs on such rows
 };
+
+// Sides with compiled row bodies: in FP32 those of the batch and of the smallest
+// images, in FP64 the powers of two from 256 on. (The halved columns have their own.)
+// Every other side runs the runtime radices, in FP64 64^2, N = 32 82 -> 53 us against
+// the five passes, 192^2, N = 32 124 -> 83, 768^2, N = 16 309 -> 209, in FP32 192^2,
+// N = 32 72 -> 34; bodies for them have not been measured.
+__host__ __device__ constexpr bool pair_rows_compiled(int M, int rsize) {
+    return M == 256 || M == 512 || M == 1024 || (rsize == 4 && (M == 64 || M == 128 || M == 384 || M == 768));
+}
 
 // Elements per thread of a row workgroup: 8 while that fits in its threads
 // (1024^2 forward rows, 8192 elements: 16 is faster, 46 -> 38 us).
@@ -1231,6 +1241,16 @@ __host__ __device__ constexpr int pair_fwd_rows(int M, int rsize) {
 // N = 32: 104 -> 98 us), the projection halves its tiles until they do (512^2,
 // N = 40: 193 -> 184 us).  Blocks of 4 or 16 rows: 482 -> 559 and 493 us for
 // the whole of 1024^2, N = 32.
+//
+// A mesh point of a restoration on one row of every pair per workgroup saves the
+// volume's way through memory, but where the rows outnumber the compute units it
+// loses to the volume's own tiles once a row leaves a unit no second workgroup (DR,
+// whose growth and mix stand between the two transforms) or has more than 16 pairs
+// on runtime radices.  Interval, whole rows against volume: DR FP32 1024^2, N = 16 / 20
+// / 30 165 / 257 / 395 against 167 / 233 / 352 us, 648^2, N = 30 299 / 254, FP64 576^2,
+// N = 16 222 / 193, 512^2, N = 20 120 / 113, FP32 512^2, N = 32 90 / 88 (two per unit),
+// FP64 256^2, N = 48 76 / 89 (a unit each); SR FP32 288^2, N = 32 / 64 72 / 169 against
+// 74 / 147, 1024^2, N = 30 278 / 319.
 inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     PairGeom g{};
     const int np = pair_count(N);
@@ -1285,6 +1305,8 @@ inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     // one row of every pair is no larger than a column block of the middle pass
     g.all_ept = np * M <= 8 * most ? 8 : 16;
     g.all_threads = pair_threads(np * M, g.all_ept);
+    g.whole_sr = M <= num_cu || pair_rows_compiled(M, rsize) || np <= 16;
+    g.whole_dr = M <= num_cu || (g.whole_sr && 2 * pair_lds_bytes(M, np, rsize) <= (size_t)kPairLds);
     return g;
 }
 

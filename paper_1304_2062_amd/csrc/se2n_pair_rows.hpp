@@ -82,20 +82,17 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_dr(co
                              tw, buf, tid, nthr);
 }
 
-// f(std::integral_constant<int, MS>) for the compiled side of M, or 0
+// f(std::integral_constant<int, MS>) for the compiled side of M (pair_rows_compiled), or 0
 template <class R, class F>
 hipError_t by_side(int M, F&& f) {
     switch (M) {
-        case 256: return f(std::integral_constant<int, 256>{});
-        case 512: return f(std::integral_constant<int, 512>{});
-        case 1024: return f(std::integral_constant<int, 1024>{});
+#define SE2N_SIDE(m)                                                                                        \
+    case m:                                                                                                 \
+        if constexpr (pair_rows_compiled(m, (int)sizeof(R))) return f(std::integral_constant<int, m>{});    \
+        break;
+        SE2N_SIDE(64) SE2N_SIDE(128) SE2N_SIDE(256) SE2N_SIDE(384) SE2N_SIDE(512) SE2N_SIDE(768) SE2N_SIDE(1024)
+#undef SE2N_SIDE
         default: break;
-    }
-    if constexpr (sizeof(R) == 4) {
-        if (M == 64) return f(std::integral_constant<int, 64>{});
-        if (M == 128) return f(std::integral_constant<int, 128>{});
-        if (M == 384) return f(std::integral_constant<int, 384>{});
-        if (M == 768) return f(std::integral_constant<int, 768>{});
     }
     return f(std::integral_constant<int, 0>{});
 }

@@ -816,7 +816,7 @@ int restore_impl(se2n_plan p, const R* f, const uint8_t* mask, double sigma, dou
                    "lift + row FFT");
     }
     for (int i = 0; i < n_int; ++i) {
-        if (p->pair && !p->pg.lay.halved) {
+        if (p->pair && (dynamic ? p->pg.whole_dr : p->pg.whole_sr)) {
             // a mesh point on whole rows of every pair in LDS
             if (i > 0 && dynamic)
                 SE2N_TIMED(p, "dr_step", st,
