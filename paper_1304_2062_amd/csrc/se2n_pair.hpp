@@ -1191,7 +1191,7 @@ __device__ __forceinline__ void pair_dr_tile(const R* __restrict__ vol, const R*
 struct PairGeom {
     PairLay lay;
     int fwd_rows, fwd_threads, fwd_ept, fwd_pairs;  // forward rows: rows, threads, pairs per workgroup
-    int vol_pairs;                                  // inverse rows to a volume: the forward tile, pairs per workgroup
+    int vol_fwd_pairs, vol_pairs;                   // a volume's rows: the forward tile, pairs per workgroup each way
     int inv_rows, inv_G, inv_threads, inv_ept;      // projecting inverse rows: all pairs, G at a time
     int mid_threads, mid_ept, mid_grid;             // middle pass; column blocks, or walkers
     int all_threads, all_ept;                       // one row of all pairs (restoration)
@@ -1236,6 +1236,11 @@ __host__ __device__ constexpr int pair_fwd_rows(int M, int rsize) {
 // many pairs per round as leave the workgroups of a unit resident together
 // (768^2, N = 24: three of 6 pairs 24 us, two of 12 pairs 35 us).
 //
+// A volume's forward rows at 1024^2 take as many pairs per workgroup as leave one
+// round of the two workgroups that a unit holds: N = 16 / 24 / 32 33 / 46 / 77 us; with
+// up to four per unit in all, as the lift, 33 / 51 / 79 (768^2, N = 32, 64 us that way
+// against 49, keeps the lift's).
+//
 // Halved columns (FP64): a tile's rows n and n + M/2 are half as many of each,
 // one workgroup lifts every pair where the tiles fill the units (1024^2,
 // N = 32: 104 -> 98 us), the projection halves its tiles until they do (512^2,
@@ -1245,12 +1250,13 @@ __host__ __device__ constexpr int pair_fwd_rows(int M, int rsize) {
 // A mesh point of a restoration on one row of every pair per workgroup saves the
 // volume's way through memory, but where the rows outnumber the compute units it
 // loses to the volume's own tiles once a row leaves a unit no second workgroup (DR,
-// whose growth and mix stand between the two transforms) or has more than 16 pairs
-// on runtime radices.  Interval, whole rows against volume: DR FP32 1024^2, N = 16 / 20
-// / 30 165 / 257 / 395 against 167 / 233 / 352 us, 648^2, N = 30 299 / 254, FP64 576^2,
-// N = 16 222 / 193, 512^2, N = 20 120 / 113, FP32 512^2, N = 32 90 / 88 (two per unit),
-// FP64 256^2, N = 48 76 / 89 (a unit each); SR FP32 288^2, N = 32 / 64 72 / 169 against
-// 74 / 147, 1024^2, N = 30 278 / 319.
+// whose growth and mix stand between the two transforms) or, on runtime radices, has
+// more than 16 pairs (DR in FP32: takes 16 elements per thread).  Interval, whole
+// rows against volume: DR FP32 1024^2, N = 16 / 20 / 30 165 / 257 / 395 against 167 / 233 /
+// 352 us, 648^2, N = 30 299 / 254, 864^2, N = 16 / 20 214 / 338 against 227 / 324, FP64
+// 576^2, N = 16 222 / 193, 512^2, N = 20 120 / 113, FP32 512^2, N = 32 90 / 88 (two per
+// unit), FP64 256^2, N = 48 76 / 89 (a unit each); SR FP32 288^2, N = 32 / 64 72 / 169
+// against 74 / 147, 1024^2, N = 30 278 / 319.
 inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     PairGeom g{};
     const int np = pair_count(N);
@@ -1267,6 +1273,13 @@ inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     int ppw = g.lay.halved && blocks >= num_cu ? np : 1;
     while (ppw < np && (long)blocks * ((np + ppw - 1) / ppw) > 4L * num_cu) ++ppw;
     g.fwd_pairs = ppw;
+    g.vol_fwd_pairs = ppw;
+    if (rsize == 4 && M == 1024)
+        while (g.vol_fwd_pairs < np && (long)blocks * ((np + g.vol_fwd_pairs - 1) / g.vol_fwd_pairs) > 2L * num_cu)
+            ++g.vol_fwd_pairs;
+    // a halved volume's pairs share nothing and go to more workgroups than the
+    // lift's (1024^2, N = 32, FP64: 184 -> 141 us)
+    if (g.lay.halved && ppw > 4) g.vol_fwd_pairs = 4;
     g.vol_pairs = 1;
     if (g.lay.halved) {
         g.inv_rows = rows;
@@ -1305,8 +1318,9 @@ inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     // one row of every pair is no larger than a column block of the middle pass
     g.all_ept = np * M <= 8 * most ? 8 : 16;
     g.all_threads = pair_threads(np * M, g.all_ept);
+    const bool many = !pair_rows_compiled(M, rsize) && rsize == 4 && g.all_ept == 16;
     g.whole_sr = M <= num_cu || pair_rows_compiled(M, rsize) || np <= 16;
-    g.whole_dr = M <= num_cu || (g.whole_sr && 2 * pair_lds_bytes(M, np, rsize) <= (size_t)kPairLds);
+    g.whole_dr = M <= num_cu || (g.whole_sr && !many && 2 * pair_lds_bytes(M, np, rsize) <= (size_t)kPairLds);
     return g;
 }
 

@@ -116,10 +116,7 @@ template <class R>
 hipError_t launch_pair_fwd(int src, const R* f, const uint8_t* mask, const uint8_t* rmap, const R* vol, C2<R>* spec,
                            int M, int N, const PairGeom& g, const FftPlan& planM, const C2<R>* tw, hipStream_t st) {
     const int np = pair_count(N);
-    // with halved columns one workgroup lifts every pair of its rows (pair_geom);
-    // a volume's pairs share nothing and go to more workgroups (1024^2, N = 32,
-    // FP64: 184 -> 141 us)
-    const int ppw = src == PSRC_VOLUME && g.lay.halved && g.fwd_pairs > 4 ? 4 : g.fwd_pairs;
+    const int ppw = src == PSRC_VOLUME ? g.vol_fwd_pairs : g.fwd_pairs;
     const dim3 grid((unsigned)(M / g.fwd_rows * ((np + ppw - 1) / ppw)));
     const size_t lds = pair_lds_bytes(M, g.fwd_rows, (int)sizeof(R));
     if constexpr (sizeof(R) == 8) {
