@@ -86,7 +86,7 @@ __global__ __launch_bounds__(1024) void kb_pair_mid(const BItem* __restrict__ it
         long step;
         C* col = pair_col<float>(d.spec, d.lay, MS, d.N, tl.y, tl.z, step);
         if (!WALK) in.load(col, step, d.lay, d.N, pair_hs(d.N), tid, nthr);
-        pair_mid_run<float, MS, EPT>(in, col, step, d.lay, d.P, d.N, tl.y, tl.z, tw, buf, tid, nthr, [&] {
+        pair_mid_run<float, MS, EPT, false, false>(in, col, step, d.lay, d.P, d.N, tl.y, tl.z, tw, buf, tid, nthr, [&] {
             if (WALK && t + (int)gridDim.x < ntiles) fetch(t + gridDim.x, tid);
         });
     }

@@ -177,16 +177,26 @@ __device__ __forceinline__ void pair_load_tw(C2<R>* tw, const C2<R>* __restrict_
     }
 }
 
-// Inputs r of a butterfly times w^{r e} (see apply_twiddles); radix 16 reads
-// six powers and forms the others by one product each.
-template <class R, int RADIX, bool INV>
+// Whether the transforms that a restoration repeats read every twiddle power.  A
+// product of two powers has twice the rounding, and the same twiddles are applied
+// at every mesh point, where their rounding adds up: 256^2, N = 30, 200 intervals of
+// SR in FP32, error 5.5e-7 with every power read, 9.3e-7 with powers formed from three
+// reads (8.0e-7 on the five passes), 5970 against 5958 us.  In FP64 the error is the
+// same either way (1.1e-15) and the reads cost 2 %.  At 16 elements per thread they
+// cost more (1024^2, N = 32 inpaint 240 -> 270 us), and so do they in the lift, volume and
+// projecting rows, which meet an image once (768^2, N = 24 inpaint 115 -> 135 us).
+__host__ __device__ constexpr bool pair_direct(int EPT, int rsize) { return rsize == 4 && EPT < 16; }
+
+// Inputs r of a butterfly times w^{r e} (see apply_twiddles); DIRECT: every power
+// read.  Radix 16 reads six powers and forms the others by one product each.
+template <class R, int RADIX, bool INV, bool DIRECT>
 __device__ __forceinline__ void pair_twiddles(C2<R>* v, const C2<R>* tw, int e, int M4) {
+    auto rd = [&](int m) {
+        C2<R> w = tw[tw_pos(m)];
+        if (INV) w.y = -w.y;
+        return w;
+    };
     if constexpr (RADIX == 16) {
-        auto rd = [&](int m) {
-            C2<R> w = tw[tw_pos(m)];
-            if (INV) w.y = -w.y;
-            return w;
-        };
         const C2<R> w1 = rd(e), w2 = rd(2 * e), w3 = rd(3 * e);
         v[1] = cmul<R>(v[1], w1);
         v[2] = cmul<R>(v[2], w2);
@@ -199,8 +209,19 @@ __device__ __forceinline__ void pair_twiddles(C2<R>* v, const C2<R>* tw, int e, 
             v[g + 2] = cmul<R>(v[g + 2], cmul<R>(wg, w2));
             v[g + 3] = cmul<R>(v[g + 3], cmul<R>(wg, w3));
         }
-    } else {
+    } else if constexpr (!DIRECT) {
         apply_twiddles<R, RADIX, INV, true>(v, tw, e, M4);
+    } else {
+        // r e lies below 3M/4, the end of the table, but for r = 7 of radix 8:
+        // w^{7e} = -w^{7e - M/2} from M/2 on
+#pragma unroll
+        for (int r = 1; r < (RADIX == 8 ? 7 : RADIX); ++r) v[r] = cmul<R>(v[r], rd(r * e));
+        if constexpr (RADIX == 8) {
+            const bool hi = 7 * e >= 2 * M4;
+            C2<R> w = rd(hi ? 7 * e - 2 * M4 : 7 * e);
+            if (hi) w = cmk<R>(-w.x, -w.y);
+            v[7] = cmul<R>(v[7], w);
+        }
     }
 }
 
@@ -262,7 +283,7 @@ struct PairLay {
 // inputs j + r L/RADIX of butterfly j of transform t, out(t, o, v, i) takes its
 // outputs o + r NS (i: the thread's i-th butterfly).  `fence`: a barrier between the two, for stages that read
 // and write the same LDS buffer.  nt L <= EPT nthr.
-template <class R, int RADIX, bool INV, int L, int NS, int EPT, class In, class Out>
+template <class R, int RADIX, bool INV, int L, int NS, int EPT, bool DIRECT, class In, class Out>
 __device__ __forceinline__ void pair_stage(const C2<R>* tw, int nt, int tid, int nthr, In&& in, Out&& out,
                                            bool fence) {
     constexpr int NB = L / RADIX;
@@ -287,7 +308,7 @@ __device__ __forceinline__ void pair_stage(const C2<R>* tw, int nt, int tid, int
             const int j = b - t * NB;
             const int q = j / NS;
             const int k = j - q * NS;
-            if (NS > 1) pair_twiddles<R, RADIX, INV>(v[i], tw, k * TWSTEP, L / 4);
+            if (NS > 1) pair_twiddles<R, RADIX, INV, DIRECT>(v[i], tw, k * TWSTEP, L / 4);
             pair_dft<R, RADIX, INV>(v[i]);
             out(t, q * NS * RADIX + k, v[i], i);
         }
@@ -306,7 +327,7 @@ __device__ __forceinline__ int pair_pos(int M, int t, int i) {
 // write of the last stage (Identity: write LDS).  Ends with a barrier exactly
 // when the result is in LDS.
 struct PairLds {};
-template <class R, bool INV, int L, int EPT, int S, int NS, class First, class Last>
+template <class R, bool INV, int L, int EPT, int S, int NS, bool DIRECT, class First, class Last>
 __device__ __forceinline__ void pair_fft_from(C2<R>* buf, const C2<R>* tw, int nt, int tid, int nthr, First&& first,
                                               Last&& last) {
     constexpr int RADIX = pair_radix(L, EPT, S);
@@ -345,19 +366,19 @@ __device__ __forceinline__ void pair_fft_from(C2<R>* buf, const C2<R>* tw, int n
                 last(t, o, v, i);
             }
         };
-        pair_stage<R, RADIX, INV, L, NS, EPT>(tw, nt, tid, nthr, in, out, IN_LDS);
+        pair_stage<R, RADIX, INV, L, NS, EPT, DIRECT>(tw, nt, tid, nthr, in, out, IN_LDS);
         if constexpr (OUT_LDS) __syncthreads();
-        pair_fft_from<R, INV, L, EPT, S + 1, NS * RADIX>(buf, tw, nt, tid, nthr, first, last);
+        pair_fft_from<R, INV, L, EPT, S + 1, NS * RADIX, DIRECT>(buf, tw, nt, tid, nthr, first, last);
     }
 }
 
 // Transforms of nt sequences in LDS, in place (compiled length MS, or the
 // runtime plan).
-template <class R, bool INV, int MS, int EPT>
+template <class R, bool INV, int MS, int EPT, bool DIRECT>
 __device__ __forceinline__ void pair_fft(C2<R>* buf, const C2<R>* tw, int M, int nt, const FftPlan& plan, int tid,
                                          int nthr) {
     if constexpr (MS != 0) {
-        pair_fft_from<R, INV, MS, EPT, 0, 1>(buf, tw, nt, tid, nthr, PairLds{}, PairLds{});
+        pair_fft_from<R, INV, MS, EPT, 0, 1, DIRECT>(buf, tw, nt, tid, nthr, PairLds{}, PairLds{});
     } else {
         fft_lds<R, INV, EPT, true>(buf, plan, nt, M + 2, tw, M >> 2, tid, nthr);
     }
@@ -532,7 +553,7 @@ struct PairMidIn {
 // The rest of a column block of a compiled side, the stage-0 inputs in `in`:
 // `next` runs before the inverse transform, whose last stage stores the
 // column from registers (no LDS is read after its barrier).
-template <class R, int MS, int EPT, bool HALF = false, class In, class Next>
+template <class R, int MS, int EPT, bool HALF, bool DIRECT, class In, class Next>
 __device__ __forceinline__ void pair_mid_run(In& in, C2<R>* __restrict__ col, long step,
                                              const PairLay& lay, const R* __restrict__ T, int N, int kx, int blk, const C2<R>* tw,
                                              C2<R>* buf, int tid, int nthr, Next&& next, int par = 0) {
@@ -542,12 +563,12 @@ __device__ __forceinline__ void pair_mid_run(In& in, C2<R>* __restrict__ col, lo
     const uint8_t* flags = reinterpret_cast<const uint8_t*>(T + pair_table_entries(MF, N, HALF));
     in.stage0(buf, hs, tid, nthr);
     __syncthreads();
-    pair_fft_from<R, false, MS, EPT, 1, In::R0>(buf, tw, hs, tid, nthr, PairLds{}, PairLds{});
+    pair_fft_from<R, false, MS, EPT, 1, In::R0, DIRECT>(buf, tw, hs, tid, nthr, PairLds{}, PairLds{});
     pair_solve<R, EPT / 4, MS, HALF>(buf, T, flags, MS, N, kx, blk, tid, par);
     __syncthreads();
     next();
     const long rstep = lay.row(MS / RL, MF / 2, N);
-    pair_fft_from<R, true, MS, EPT, 0, 1>(buf, tw, hs, tid, nthr, PairLds{}, [&](int t, int o, C2<R>* w, int) {
+    pair_fft_from<R, true, MS, EPT, 0, 1, DIRECT>(buf, tw, hs, tid, nthr, PairLds{}, [&](int t, int o, C2<R>* w, int) {
         C2<R>* g = col + t * step + lay.row(o, MF / 2, N);
 #pragma unroll
         for (int r = 0; r < RL; ++r) g[r * rstep] = w[r];
@@ -570,10 +591,10 @@ __device__ __forceinline__ void pair_mid_generic(C2<R>* __restrict__ spec, const
         buf[pair_pos<0>(M, t, y)] = col[t * step + lay.row(y, M >> 1, N)];
     }
     __syncthreads();
-    pair_fft<R, false, 0, EPT>(buf, tw, M, hs, planM, tid, nthr);
+    pair_fft<R, false, 0, EPT, false>(buf, tw, M, hs, planM, tid, nthr);
     pair_solve<R, EPT / 4, 0>(buf, T, flags, M, N, kx, blk, tid);
     __syncthreads();
-    pair_fft<R, true, 0, EPT>(buf, tw, M, hs, planM, tid, nthr);
+    pair_fft<R, true, 0, EPT, false>(buf, tw, M, hs, planM, tid, nthr);
     for (int e = tid; e < hs * M; e += nthr) {
         const int t = fdiv(e, inv_M);
         const int y = e - t * M;
@@ -936,7 +957,7 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
             __syncthreads();
             if constexpr (SRC == PSRC_VOLUME)
                 if (t + 1 < t_end) inputs(t + 1);
-            pair_fft_from<R, false, MS, EPT, 1, R0>(buf, tw, rows, tid, nthr, PairLds{}, PairLds{});
+            pair_fft_from<R, false, MS, EPT, 1, R0, false>(buf, tw, rows, tid, nthr, PairLds{}, PairLds{});
             if constexpr (HALF) pair_unpack_half<R, MS>(buf, spec, lay, N, t, rows, y0, tw, tid, nthr);
             else pair_unpack<R, MS>(buf, spec, lay, M, N, t, 0, rows, y0, tid, nthr);
             __syncthreads();
@@ -957,7 +978,7 @@ __device__ __forceinline__ void pair_fwd_tile(const R* __restrict__ f, const uin
                 buf[pair_pos<0>(M, row, n)] = z;
             }
             __syncthreads();
-            pair_fft<R, false, 0, EPT>(buf, tw, M, rows, planM, tid, nthr);
+            pair_fft<R, false, 0, EPT, false>(buf, tw, M, rows, planM, tid, nthr);
             pair_unpack<R, 0>(buf, spec, lay, M, N, t, 0, rows, y0, tid, nthr);
             __syncthreads();
         }
@@ -990,7 +1011,8 @@ __device__ __forceinline__ void pair_inv_tile(C2<R>* __restrict__ spec, const Pa
         const int np = min(G, t_end - t0);
         pair_pack<R, MS>(buf, spec, lay, M, N, t0, np, rows, y0, tid, nthr);
         __syncthreads();
-        pair_fft<R, true, MS, EPT>(buf, tw, M, np * rows, planM, tid, nthr);
+        constexpr bool DIRECT = pair_direct(EPT, (int)sizeof(R)) && (DST == PDST_SR || DST == PDST_VOLMAX);
+        pair_fft<R, true, MS, EPT, DIRECT>(buf, tw, M, np * rows, planM, tid, nthr);
 #pragma unroll 1
         for (int e = tid; e < npx; e += nthr) {
             const int row = MS ? e / (MS ? MS : 1) : fdiv(e, inv_M);
@@ -1037,7 +1059,7 @@ __device__ __forceinline__ void pair_inv_tile(C2<R>* __restrict__ spec, const Pa
         }
         __syncthreads();
         if constexpr (DST == PDST_SR) {
-            pair_fft<R, false, MS, EPT>(buf, tw, M, np * rows, planM, tid, nthr);
+            pair_fft<R, false, MS, EPT, DIRECT>(buf, tw, M, np * rows, planM, tid, nthr);
             for (int g = 0; g < np; ++g)
                 // the inverse pass leaves p/2 and q/2 (the propagators carry the
                 // 1/2 of x = (p +- q) / 2)
@@ -1077,7 +1099,7 @@ __device__ __forceinline__ void pair_inv_half_tile(const C2<R>* __restrict__ spe
         __syncthreads();
         if (t + 1 < t_end) in.load(spec, lay, N, t + 1, rows, y0, tid, nthr);
         const bool two = !odd || 2 * t + 1 < N;
-        pair_fft_from<R, true, MS, EPT, 0, 1>(buf, tw, rows, tid, nthr, PairLds{}, [&](int row, int o, C2<R>* v, int i) {
+        pair_fft_from<R, true, MS, EPT, 0, 1, false>(buf, tw, rows, tid, nthr, PairLds{}, [&](int row, int o, C2<R>* v, int i) {
             if constexpr (DST == PDST_VOLUME) {
                 R* q = out + (size_t)pair_image_row<true>(M, rows, y0, row) * M + o;
                 R* qa = q + (size_t)(odd ? 2 * t : t) * img;
@@ -1180,7 +1202,7 @@ __device__ __forceinline__ void pair_dr_tile(const R* __restrict__ vol, const R*
         }
     }
     __syncthreads();
-    pair_fft<R, false, MS, EPT>(buf, tw, M, np * rows, planM, tid, nthr);
+    pair_fft<R, false, MS, EPT, pair_direct(EPT, (int)sizeof(R))>(buf, tw, M, np * rows, planM, tid, nthr);
     for (int g = 0; g < np; ++g)
         pair_unpack<R, MS>(buf, spec, lay, M, N, g, g * rows, rows, y0, tid, nthr);
 }

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_mid(C
                 pair_mid_col(i + gridDim.x, H, nblk, kn, bn);
                 cn = pair_col<R>(spec, lay, M, N, kn, bn, step);
             }
-            pair_mid_run<R, MS, EPT>(in, col, step, lay, T, N, kx, blk, tw, buf, tid, nthr, [&] {
+            pair_mid_run<R, MS, EPT, false, pair_direct(EPT, (int)sizeof(R))>(in, col, step, lay, T, N, kx, blk, tw, buf, tid, nthr, [&] {
                 if (more) in.load(cn, step, lay, N, hs, tid, nthr);
             });
             if (!more) return;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_mid_h
         const int k0 = kx, b0 = blk, p0 = par;
         C2<R>* cn = col;
         if (more) cn = column(i + gridDim.x);
-        pair_mid_run<R, MS, EPT, true>(
+        pair_mid_run<R, MS, EPT, true, false>(
             in, col, step, lay, T, N, k0, b0, tw, buf, tid, nthr,
             [&] {
                 if (more) in.load(cn, step, lay, N, hs, tid, nthr);
