@@ -335,9 +335,10 @@ typedef struct {
 } se2n_item;
 
 /* Schedule of a batch (what the autotuner chooses).
+ * It orders the orientation and the five passes; the three-pass groups always
+ * launch one workgroup per tile, or their own walkers, image after image.
  *   wg_per_cu   persistent workgroups per compute unit for every pass
- *               (1..16); 0 launches one workgroup per tile instead, as the
- *               three-pass groups always do.
+ *               (1..16); 0 launches one workgroup per tile instead.
  *   order       0: tiles of each pass sorted by decreasing cost (largest
  *               first), 1: image by image in item order.
  *   row_groups  slice groups of the lift and inverse row passes (1..64,
@@ -352,9 +353,9 @@ typedef struct {
 } se2n_tune;
 
 /* Device workspace bytes se2n_inpaint_batched needs for these items: per
- * item the half-spectrum volume (two for sides 512, 768 and 1024, whose inverse
- * passes go through a row-blocked copy), a max-combining buffer and an
- * orientation map.  Returns 0 if an item is invalid (see se2n_last_error). */
+ * item the half-spectrum volume (two for sides 512, 768 and 1024: the five passes
+ * go through a row-blocked copy, which images on the three passes leave unused), a
+ * max-combining buffer and an orientation map.  Returns 0 if an item is invalid (see se2n_last_error). */
 size_t se2n_batch_workspace_bytes(const se2n_item *items, int count);
 
 /* Inpaint every item (see above).  workspace: at least
@@ -365,7 +366,8 @@ int se2n_inpaint_batched(const se2n_item *items, int count, void *workspace, voi
 /* Autotuner: time the batch under each candidate schedule (wg_per_cu in
  * {0, 1, 2, 4} x order in {0, 1} x row_groups in {1, 2, 4}), `reps` graph
  * launches each after one warm-up, on `stream` (this call synchronises it),
- * and keep the fastest for this signature.  If table_path is non-NULL the
+ * and keep the fastest for this signature (a batch all on the three passes differs
+ * between candidates in its orientation only).  If table_path is non-NULL the
  * choice is also written there (one JSON object per line, keyed by the
  * device's architecture name and the signature hash; an existing entry for
  * the key is replaced).  best / best_ms may be NULL.  The items' outputs
@@ -392,7 +394,8 @@ int se2n_batch_set_tune(const se2n_item *items, int count, const se2n_tune *tune
 int se2n_batch_get_tune(const se2n_item *items, int count, se2n_tune *out);
 
 /* The tile list of one pass of a batch under `tune` (NULL: the current
- * schedule) with every image on the five passes, in execution order, 4 ints per tile {item, a, b, c}:
+ * schedule) with every image on the five passes, in execution order, 4 ints per
+ * tile {item, a, b, c}:
  *   pass 0 orientation rows     {item, row block, 0, 1}
  *   pass 1 orientation columns  {item, first column kx, 0, 0}
  *   pass 2 orientation inverse  {item, row block, 0, 2}

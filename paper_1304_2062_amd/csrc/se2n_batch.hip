@@ -4,8 +4,7 @@
 // part of that image's work (row block and slice range, first column, class
 // block, pixel range).  The image's twiddle table is expanded into LDS only
 // when the previous tile of the workgroup belonged to an image of another
-// table.  The tile bodies are the ones the single-image kernels run; images
-// of side 512 and 1024 use the bodies compiled for those sizes.
+// table.  The tile bodies are the ones the single-image kernels run.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -73,9 +72,9 @@ __device__ __forceinline__ T uni(T v) {
     return v;
 }
 
-// The row and column kernels come in three size classes, each launched over
-// the tiles of its own images: MS = 1024 and MS = 512 run the bodies compiled
-// for that side, MS = 0 the generic body for every other side.
+// The row and column kernels come in size classes (kBatchSides), each launched
+// over the tiles of its own images: MS > 0 runs the body compiled for that side,
+// MS = 0 the generic body for every other side.
 template <int SRC, int MS>
 __global__ __launch_bounds__(BT) __attribute__((amdgpu_waves_per_eu(4))) void kb_row_fwd(const BItem* __restrict__ items, const int4* __restrict__ tiles,
                                                  int ntiles) {
@@ -260,6 +259,23 @@ struct SolveCfg {
         default: return f((const void*)KT(0), NT<0>());                                \
     }
 static_assert(kBatchClasses == 8 && kBatchSides[1] == 128 && kBatchSides[7] == 1024, "class table");
+// The five separate passes, which images on the pair path do not take: every image
+// of the classes 1 .. 5 does.
+#define SE2N_FIVE_BY_CLASS(KT, NT)                                                     \
+    switch (cls) {                                                                     \
+        case 0: return f((const void*)KT(0), NT<0>());                                 \
+        case 6: return f((const void*)KT(768), NT<768>());                             \
+        case 7: return f((const void*)KT(1024), NT<1024>());                           \
+        default: return hipErrorInvalidValue;                                          \
+    }
+constexpr bool always_on_pair_path(int c) {
+    for (int N = 4; N <= 64; N += 2)
+        if (!pair_fits(kBatchSides[c], N, 4)) return false;
+    return true;
+}
+static_assert(always_on_pair_path(1) && always_on_pair_path(2) && always_on_pair_path(3) && always_on_pair_path(4) &&
+                  always_on_pair_path(5),
+              "the classes without five passes");
 
 template <class F>
 hipError_t with_kernel(int kind, int N, int cls, F&& f) {
@@ -271,7 +287,7 @@ hipError_t with_kernel(int kind, int N, int cls, F&& f) {
         }
         case BK_LIFT_ROW: {
 #define K_(m) kb_row_fwd<SRC_LIFT, m>
-            SE2N_BY_CLASS(K_, row_nt)
+            SE2N_FIVE_BY_CLASS(K_, row_nt)
 #undef K_
         }
         case BK_ORIENT_COL: return f((const void*)kb_col_orient, BT);
@@ -282,22 +298,22 @@ hipError_t with_kernel(int kind, int N, int cls, F&& f) {
         }
         case BK_ROW_INV_MAX: {
 #define K_(m) kb_row_inv<DST_MAX, m, true>
-            SE2N_BY_CLASS(K_, row_nt)
+            SE2N_FIVE_BY_CLASS(K_, row_nt)
 #undef K_
         }
         case BK_ROW_INV_MEAN: {
 #define K_(m) kb_row_inv<DST_SUM, m, true>
-            SE2N_BY_CLASS(K_, row_nt)
+            SE2N_FIVE_BY_CLASS(K_, row_nt)
 #undef K_
         }
         case BK_COL_FWD: {
 #define K_(m) kb_col_fft<false, m>
-            SE2N_BY_CLASS(K_, col_nt)
+            SE2N_FIVE_BY_CLASS(K_, col_nt)
 #undef K_
         }
         case BK_COL_INV: {
 #define K_(m) kb_col_inv_paired<m>
-            SE2N_BY_CLASS(K_, pcol_nt)
+            SE2N_FIVE_BY_CLASS(K_, pcol_nt)
 #undef K_
         }
         case BK_ORIENT_STENCIL:
@@ -330,6 +346,7 @@ hipError_t with_kernel(int kind, int N, int cls, F&& f) {
     }
 }
 #undef SE2N_BY_CLASS
+#undef SE2N_FIVE_BY_CLASS
 
 }  // namespace
 

@@ -22,7 +22,7 @@ struct BItem {
     float* out;
     C2<float>* spec;   // half-spectrum volume [N][M/2+1][M] (workspace)
     C2<float>* blk;    // row-blocked second volume between the inverse passes
-                       // (sides with batch_two_buf, else null; workspace)
+                       // (sides with batch_blocked, else null; workspace)
     unsigned* enc;     // max-combining buffer [M][M] (workspace)
     const float* P;    // propagator table of (M, N, T, beta, n, scheme)
     const C2<float>* tw;  // quarter-wave twiddles of M
@@ -80,13 +80,16 @@ inline int batch_class(int M) {
 template <int MS>
 constexpr bool kBatchTwoBuf = MS == 512 || MS == 1024;
 inline bool batch_two_buf(int M) { return M == 512 || M == 1024; }
-// Sides whose inverse passes go through a row-blocked second volume (as the
+// Sides whose five passes go through a row-blocked second volume (as the
 // single-image path does): the inverse column pass writes it, the inverse
 // row pass reads it in 64-byte pieces of consecutive lines.
 template <int MS>
-constexpr bool kBatchBlocked = MS == 512 || MS == 768 || MS == 1024;
+constexpr bool kBatchBlocked = MS == 768 || MS == 1024;
+// Sides whose items have room for a second volume in the workspace.  Items on the
+// pair path (all of 512, most of the others) leave theirs unused; its size is
+// part of what se2n_batch_workspace_bytes has always returned.
 inline bool batch_blocked(int M) { return M == 512 || M == 768 || M == 1024; }
-static_assert(512 % kRowBlk == 0 && 768 % kRowBlk == 0 && 1024 % kRowBlk == 0, "row blocks of the blocked sides");
+static_assert(768 % kRowBlk == 0 && 1024 % kRowBlk == 0, "row blocks of the blocked sides");
 
 // Items that run their three passes on the pair path (se2n_pair.hpp): compiled
 // sides whose columns fit.  The other sides keep the five separate passes: the
