@@ -243,8 +243,9 @@ __host__ __device__ constexpr int tw_elems(int M, bool full) {
 // Multiply inputs r = 1 .. RADIX-1 of a butterfly by w^{r e} (conjugated for
 // the inverse).  Only w^e, w^{2e} (and w^{4e} for radix 8) are read from the
 // LDS table; the other powers are products of those, which saves LDS reads
-// at an error of a few ulps.
-template <class R, int RADIX, bool INV, bool TWFULL>
+// at an error of a few ulps.  DIRECT: all of them are read, from a table of at
+// least 3M/4 entries.
+template <class R, int RADIX, bool INV, bool TWFULL, bool DIRECT = false>
 __device__ __forceinline__ void apply_twiddles(C2<R>* v, const C2<R>* twq, int e, int M4) {
     // In a stage of radix RADIX the exponent e = k M / (Ns RADIX), k < Ns,
     // lies below M / RADIX, which bounds the quadrant of each power read.
@@ -261,6 +262,17 @@ __device__ __forceinline__ void apply_twiddles(C2<R>* v, const C2<R>* twq, int e
     } else if constexpr (RADIX == 3) {
         v[1] = cmul<R>(v[1], rd(Q1{}, e));      // e < M/3
         v[2] = cmul<R>(v[2], rd(Q2{}, 2 * e));  // 2e < 2M/3
+    } else if constexpr (DIRECT) {
+        static_assert(TWFULL, "powers beyond the quarter table");
+        // r e lies below 3M/4 but for r = 7 of radix 8: w^{7e} = -w^{7e - M/2} from M/2 on
+#pragma unroll
+        for (int r = 1; r < (RADIX == 8 ? 7 : RADIX); ++r) v[r] = cmul<R>(v[r], rd(Q2{}, r * e));
+        if constexpr (RADIX == 8) {
+            const bool hi = 7 * e >= 2 * M4;
+            C2<R> w = rd(Q2{}, hi ? 7 * e - 2 * M4 : 7 * e);
+            if (hi) w = cmk<R>(-w.x, -w.y);
+            v[7] = cmul<R>(v[7], w);
+        }
     } else if constexpr (RADIX == 4) {
         const C2<R> w1 = rd(Q0{}, e), w2 = rd(Q1{}, 2 * e);  // e < M/4, 2e < M/2
         v[1] = cmul<R>(v[1], w1);
@@ -287,7 +299,7 @@ __device__ __forceinline__ void apply_twiddles(C2<R>* v, const C2<R>* twq, int e
 // butterflies, the block synchronises, then every thread writes.
 // Thread tid owns butterflies b = tid + i*nthr, i.e. transform t = b / nb and
 // butterfly j = b mod nb.  The caller guarantees nbatch*L <= EPT*nthr.
-template <class R, int RADIX, bool INV, int EPT, bool TWFULL>
+template <class R, int RADIX, bool INV, int EPT, bool TWFULL, bool DIRECT>
 __device__ __forceinline__ void fft_stage(C2<R>* buf, const FftStage& s, int nbatch, int bstride,
                                           const C2<R>* twq, int M4, int tid, int nthr) {
     constexpr int MAXB = (EPT + RADIX - 1) / RADIX;
@@ -321,7 +333,7 @@ __device__ __forceinline__ void fft_stage(C2<R>* buf, const FftStage& s, int nba
     for (int i = 0; i < MAXB; ++i) {
         const int b = tid + i * nthr;
         if (b < total) {
-            if (Ns > 1) apply_twiddles<R, RADIX, INV, TWFULL>(v[i], twq, __mul24(kk[i], twstep), M4);
+            if (Ns > 1) apply_twiddles<R, RADIX, INV, TWFULL, DIRECT>(v[i], twq, __mul24(kk[i], twstep), M4);
             dft<R, RADIX, INV>(v[i]);
 #pragma unroll
             for (int r = 0; r < RADIX; ++r) buf[lds_pad(obase[i] + r * Ns)] = v[i][r];
@@ -335,17 +347,17 @@ __device__ __forceinline__ void fft_stage(C2<R>* buf, const FftStage& s, int nba
 // Forward: X_k = sum_n x_n w_L^{nk}; inverse: the same with w_L^{-nk}.
 // twq is the LDS twiddle table of the plan's side M (full period or quarter).
 // All nthr threads of the workgroup call it; it synchronises the workgroup.
-template <class R, bool INV, int EPT, bool TWFULL>
+template <class R, bool INV, int EPT, bool TWFULL, bool DIRECT = false>
 __device__ void fft_lds(C2<R>* buf, const FftPlan& plan, int nbatch, int bstride, const C2<R>* twq, int M4,
                         int tid, int nthr) {
     const int nst = __builtin_amdgcn_readfirstlane(plan.nstages);
     for (int s = 0; s < nst; ++s) {
         const FftStage& st = plan.st[s];
         const int radix = __builtin_amdgcn_readfirstlane(st.radix);
-        if (radix == 8) fft_stage<R, 8, INV, EPT, TWFULL>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
-        else if (radix == 4) fft_stage<R, 4, INV, EPT, TWFULL>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
-        else if (radix == 3) fft_stage<R, 3, INV, EPT, TWFULL>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
-        else fft_stage<R, 2, INV, EPT, TWFULL>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
+        if (radix == 8) fft_stage<R, 8, INV, EPT, TWFULL, DIRECT>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
+        else if (radix == 4) fft_stage<R, 4, INV, EPT, TWFULL, DIRECT>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
+        else if (radix == 3) fft_stage<R, 3, INV, EPT, TWFULL, DIRECT>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
+        else fft_stage<R, 2, INV, EPT, TWFULL, DIRECT>(buf, st, nbatch, bstride, twq, M4, tid, nthr);
     }
 }
 

@@ -181,11 +181,13 @@ __device__ __forceinline__ void pair_load_tw(C2<R>* tw, const C2<R>* __restrict_
 // product of two powers has twice the rounding, and the same twiddles are applied
 // at every mesh point, where their rounding adds up: 256^2, N = 30, 200 intervals of
 // SR in FP32, error 5.5e-7 with every power read, 9.3e-7 with powers formed from three
-// reads (8.0e-7 on the five passes), 5970 against 5958 us.  In FP64 the error is the
-// same either way (1.1e-15) and the reads cost 2 %.  At 16 elements per thread they
-// cost more (1024^2, N = 32 inpaint 240 -> 270 us), and so do they in the lift, volume and
-// projecting rows, which meet an image once (768^2, N = 24 inpaint 115 -> 135 us).
-__host__ __device__ constexpr bool pair_direct(int EPT, int rsize) { return rsize == 4 && EPT < 16; }
+// reads (8.0e-7 on the five passes), 5970 against 5958 us; 1024^2, N = 30 and 96^2, N = 30
+// 1.13 and 1.1 times the five passes' error without, 1.0 and 0.9 with, within 1 % of
+// the time.  In FP64 the error is the same either way (1.1e-15) and the reads cost 2 %.
+// At 16 elements per thread the middle pass keeps the products (1024^2, N = 32 inpaint
+// 240 -> 270 us), and so do the lift, volume and projecting rows, which meet an image
+// once (768^2, N = 24 inpaint 115 -> 135 us).
+__host__ __device__ constexpr bool pair_direct(int rsize) { return rsize == 4; }
 
 // Inputs r of a butterfly times w^{r e} (see apply_twiddles); DIRECT: every power
 // read.  Radix 16 reads six powers and forms the others by one product each.
@@ -209,19 +211,8 @@ __device__ __forceinline__ void pair_twiddles(C2<R>* v, const C2<R>* tw, int e, 
             v[g + 2] = cmul<R>(v[g + 2], cmul<R>(wg, w2));
             v[g + 3] = cmul<R>(v[g + 3], cmul<R>(wg, w3));
         }
-    } else if constexpr (!DIRECT) {
-        apply_twiddles<R, RADIX, INV, true>(v, tw, e, M4);
     } else {
-        // r e lies below 3M/4, the end of the table, but for r = 7 of radix 8:
-        // w^{7e} = -w^{7e - M/2} from M/2 on
-#pragma unroll
-        for (int r = 1; r < (RADIX == 8 ? 7 : RADIX); ++r) v[r] = cmul<R>(v[r], rd(r * e));
-        if constexpr (RADIX == 8) {
-            const bool hi = 7 * e >= 2 * M4;
-            C2<R> w = rd(hi ? 7 * e - 2 * M4 : 7 * e);
-            if (hi) w = cmk<R>(-w.x, -w.y);
-            v[7] = cmul<R>(v[7], w);
-        }
+        apply_twiddles<R, RADIX, INV, true, DIRECT>(v, tw, e, M4);
     }
 }
 
@@ -380,7 +371,7 @@ __device__ __forceinline__ void pair_fft(C2<R>* buf, const C2<R>* tw, int M, int
     if constexpr (MS != 0) {
         pair_fft_from<R, INV, MS, EPT, 0, 1, DIRECT>(buf, tw, nt, tid, nthr, PairLds{}, PairLds{});
     } else {
-        fft_lds<R, INV, EPT, true>(buf, plan, nt, M + 2, tw, M >> 2, tid, nthr);
+        fft_lds<R, INV, EPT, true, DIRECT>(buf, plan, nt, M + 2, tw, M >> 2, tid, nthr);
     }
 }
 
@@ -591,10 +582,10 @@ __device__ __forceinline__ void pair_mid_generic(C2<R>* __restrict__ spec, const
         buf[pair_pos<0>(M, t, y)] = col[t * step + lay.row(y, M >> 1, N)];
     }
     __syncthreads();
-    pair_fft<R, false, 0, EPT, false>(buf, tw, M, hs, planM, tid, nthr);
+    pair_fft<R, false, 0, EPT, pair_direct((int)sizeof(R)) && (EPT < 16)>(buf, tw, M, hs, planM, tid, nthr);
     pair_solve<R, EPT / 4, 0>(buf, T, flags, M, N, kx, blk, tid);
     __syncthreads();
-    pair_fft<R, true, 0, EPT, false>(buf, tw, M, hs, planM, tid, nthr);
+    pair_fft<R, true, 0, EPT, pair_direct((int)sizeof(R)) && (EPT < 16)>(buf, tw, M, hs, planM, tid, nthr);
     for (int e = tid; e < hs * M; e += nthr) {
         const int t = fdiv(e, inv_M);
         const int y = e - t * M;
@@ -1011,7 +1002,7 @@ __device__ __forceinline__ void pair_inv_tile(C2<R>* __restrict__ spec, const Pa
         const int np = min(G, t_end - t0);
         pair_pack<R, MS>(buf, spec, lay, M, N, t0, np, rows, y0, tid, nthr);
         __syncthreads();
-        constexpr bool DIRECT = pair_direct(EPT, (int)sizeof(R)) && (DST == PDST_SR || DST == PDST_VOLMAX);
+        constexpr bool DIRECT = pair_direct((int)sizeof(R)) && (DST == PDST_SR || DST == PDST_VOLMAX);
         pair_fft<R, true, MS, EPT, DIRECT>(buf, tw, M, np * rows, planM, tid, nthr);
 #pragma unroll 1
         for (int e = tid; e < npx; e += nthr) {
@@ -1202,7 +1193,7 @@ __device__ __forceinline__ void pair_dr_tile(const R* __restrict__ vol, const R*
         }
     }
     __syncthreads();
-    pair_fft<R, false, MS, EPT, pair_direct(EPT, (int)sizeof(R))>(buf, tw, M, np * rows, planM, tid, nthr);
+    pair_fft<R, false, MS, EPT, pair_direct((int)sizeof(R))>(buf, tw, M, np * rows, planM, tid, nthr);
     for (int g = 0; g < np; ++g)
         pair_unpack<R, MS>(buf, spec, lay, M, N, g, g * rows, rows, y0, tid, nthr);
 }

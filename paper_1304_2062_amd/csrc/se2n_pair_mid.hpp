@@ -43,7 +43,8 @@ __global__ __launch_bounds__(pair_max_threads((int)sizeof(R))) void k_pair_mid(C
                 pair_mid_col(i + gridDim.x, H, nblk, kn, bn);
                 cn = pair_col<R>(spec, lay, M, N, kn, bn, step);
             }
-            pair_mid_run<R, MS, EPT, false, pair_direct(EPT, (int)sizeof(R))>(in, col, step, lay, T, N, kx, blk, tw, buf, tid, nthr, [&] {
+            pair_mid_run<R, MS, EPT, false, pair_direct((int)sizeof(R)) && (EPT < 16)>(
+                in, col, step, lay, T, N, kx, blk, tw, buf, tid, nthr, [&] {
                 if (more) in.load(cn, step, lay, N, hs, tid, nthr);
             });
             if (!more) return;

@@ -8,8 +8,9 @@
 //  * every tile fits the threads, elements per thread and LDS it is launched
 //    with, its rows lie inside one block, and the compiled first and last stages
 //    step by whole blocks;
-//  * the radix sequences multiply to the length and read no twiddle beyond the
-//    3M/4 entries held in LDS.
+//  * the radix sequences of these and of every other pair plan's side multiply to
+//    the length and read no twiddle beyond the 3M/4 entries held in LDS, also
+//    where every power is read.
 // Prints "plans <count> bad <count>" and exits with 1 when any check fails.
 #include <cstdio>
 #include <vector>
@@ -29,8 +30,8 @@ static void radices(int L, int ept, int M, int N) {
     for (int s = 0; pair_radix(L, ept, s) != 0; ++s) {
         const int r = pair_radix(L, ept, s);
         const long e = prod > 1 ? (long)(prod - 1) * (L / (prod * r)) : 0;
-        const int reads = r == 16 ? 12 : r == 8 ? 4 : r == 4 ? 2 : r == 3 ? 2 : 1;
-        check(reads * e < 3 * (L / 4), "twiddle range", M, N);
+        const int reads = r == 16 ? 12 : r == 8 ? 6 : r - 1;
+        check(reads * e < 3 * (L / 4) && (r != 8 || 7 * e - L / 2 < L / 2), "twiddle range", M, N);
         check(ept >= 16 || r <= 8, "radix", M, N);
         prod *= r;
     }
@@ -38,6 +39,13 @@ static void radices(int L, int ept, int M, int N) {
 }
 
 int main() {
+    for (int M = 16; M <= 1024; M += 4) {
+        int m = M;
+        while (m % 2 == 0) m /= 2;
+        while (m % 3 == 0) m /= 3;
+        if (m == 1)
+            for (int ept : {4, 8, 16}) radices(M, ept, M, ept);
+    }
     for (int M = 16; M <= 4096; M += 4)
         for (int N = 4; N <= 64; ++N) {
             check(!pair_halves(M, N, 4), "FP32", M, N);

@@ -16,7 +16,8 @@ from paper_1304_2062_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,N,n", [(256, 30, 200), (128, 24, 100), (384, 16, 100), (512, 16, 100), (64, 64, 100)])
+@pytest.mark.parametrize("M,N,n", [(256, 30, 200), (128, 24, 100), (384, 16, 100), (512, 16, 100), (64, 64, 100), (96, 30, 100),
+                                   (1024, 24, 60)])
 def test_repeated_transforms_are_as_exact_as_on_the_five_passes(monkeypatch, M, N, n):
     from paper_1304_2062_amd import se2n
     print(f"restore error {M} {N}", flush=True)
