@@ -34,9 +34,9 @@ constexpr int kMaxItems = 4096;
 constexpr int kMaxPlansPerDevice = 4;
 constexpr int kPixelsPerTile = 8192;  // clear / decode tiles
 // The pair path's groups and branches (build_schedule), measured on 64 images
-// of 128^2..1024^2 and on 30 of 64^2..512^2: one branch 3.51 and 0.84 ms, two
-// 3.16 and 0.69, three 3.20 and 0.66, four 3.22 and 0.85; groups of 32, 64, 128
-// and 256 MB on two branches 3.18, 3.16, 3.17, 3.23 ms.
+// of 128^2..1024^2 and on 30 of 64^2..512^2: one branch 3.49 and 0.76 ms, two
+// 3.14 and 0.645, three 3.20 and 0.63, four 3.22 and 0.785; groups of 32, 64, 128
+// and 256 MB on two branches 3.19, 3.14, 3.17, 3.23 ms.
 constexpr int kPairBranches = 2;
 constexpr size_t kPairGroupBytes = (size_t)64 << 20;
 

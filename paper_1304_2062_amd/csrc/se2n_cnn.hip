@@ -177,9 +177,10 @@ __device__ __forceinline__ void net_layer(const bf16* in, const NetW<NB>& wt, in
 // A wave takes NB blocks of 16 output channels.  Two workgroups share a
 // compute unit's LDS; a layer's weights and the values that layer 3 adds to are
 // fetched one layer ahead.  At 2^20 pixels no unit is saturated: matrix cores
-// 30 %, vector instructions 40 %, LDS 45 % of the time (134 MB read and
-// written, 2.1 TB/s).  Waves of one block each hide more of that where the
-// registers allow it (inference 138 -> 127 us; training spills, 185 -> 245 us).
+// 28 %, vector instructions 38 %, LDS 42 % of the time (202 MB read with the
+// halos, 135 MB written, 2.5 TB/s).  Waves of one block each hide more of that
+// where the registers allow it (inference 138 -> 127 us; training spills,
+// 185 -> 245 us).
 // Layer by layer, with the packing, 43 + 41 + 41 + 115 us before.
 template <bool TRAIN, bool PACKED, int NB>
 __global__ __launch_bounds__(512 / NB, 4 / NB) void k_cnn_net(bf16* __restrict__ a0, const bf16* __restrict__ wf,
@@ -422,8 +423,9 @@ __device__ __forceinline__ bf16x8 tr_read(const bf16* p) {
 // gradient: its five row pairs of the input, at three column shifts, are read
 // once each and serve both products that they belong to.  The tiles are in LDS
 // as they are in memory, channels last, and transposed by the reads; the next
-// tile is fetched into registers meanwhile.  1024^2 pixels: 91 -> 39 us (134 MB, 3.4 TB/s) against
-// channel-major tiles with three shifted copies written two bytes at a time.
+// tile is fetched into registers meanwhile.  2^20 pixels: 91 -> 41 us (166 MB,
+// a fifth of it halos and partials, 4.0 TB/s) against channel-major tiles with
+// three shifted copies written two bytes at a time.
 __global__ __launch_bounds__(256, 2) void k_cnn_wgrad(const bf16* __restrict__ g, const bf16* __restrict__ a,
                                                       float* __restrict__ parts, int M, int ntiles, int tpw) {
     constexpr int NG = T * T * PS, NA = HT * HT * PS;

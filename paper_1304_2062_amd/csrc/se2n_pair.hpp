@@ -68,9 +68,12 @@ __host__ __device__ constexpr int pair_max_threads(int rsize) { return rsize == 
 // Middle pass: elements per thread, and threads: M/4 class positions times
 // the row groups of the per-mode product (ept / 4 rows of the four modes of a
 // class, see pair_solve).  8 elements, and twice the threads, up to 5120
-// elements in FP32 (324^2, N = 15 32.5 -> 26.3 us, 768^2, N = 12 28.0 -> 25.2
-// us; 6144 elements 768^2, N = 16 32.4 -> 34.9 us; a side of 1024, which takes
-// three stages with 16 and four with 8, N = 10 30.7 -> 33.4 us).
+// elements in FP32: over the plans of 4096 .. 5120 elements 1.03 .. 1.20 times as
+// fast as 16 on runtime radices (324^2, N = 15 33.6 -> 28.1 us), 0.99 .. 1.13 on compiled
+// sides (768^2, N = 12 28.5 -> 25.7).  Above, compiled sides from 256 on lose (768^2,
+// N = 16 32.3 against 35.3 us), 128, 192 and runtime radices still gain up to 5800 and
+// lose beyond (648^2, N = 18 57 against 72).  A side of 1024, which takes three stages
+// with 16 and four with 8: N = 10 30.7 against 33.4 us.
 __host__ __device__ constexpr int pair_mid_ept(int M, int hs, int rsize) {
     const int elems = hs * M;
     return elems <= 1024 ? 4 : elems <= (rsize == 4 && M < 1024 ? 5120 : 4096) ? 8 : 16;

@@ -33,7 +33,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 
 def short_name(name: str) -> str:
-    """Kernel name without the argument list and namespace."""
+    """Kernel name without the argument list and namespace (a name that the tracer
+    left mangled, as those with bfloat16 arguments are: with its literal template
+    arguments)."""
+    m = re.search(r"\d+(kb?_[a-z0-9_]+?)I((?:L[bij]\d+E)+)E", name) if name.startswith("_Z") else None
+    if m:
+        return m.group(1) + "<" + ",".join(re.findall(r"L[bij](\d+)E", m.group(2))) + ">"
     base = name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "").replace("se2n::", "")
     return re.sub(r"\s+", "", base)
 
@@ -105,11 +110,12 @@ def main(argv=None) -> int:
     c = sub.add_parser("sq", help="per-kernel averages of SQ counters from one or more --pmc runs")
     c.add_argument("dirs", nargs="+")
     c.add_argument("--cmd", required=True)
-    c.add_argument("--kernels", default="", help="comma-separated kernel name prefixes to keep")
+    for p in (a, b, c):
+        p.add_argument("--kernels", default="", help="comma-separated kernel name prefixes to keep")
     args = ap.parse_args(argv)
+    keep = [k for k in args.kernels.split(",") if k]
 
     if args.mode == "sq":
-        keep = [k for k in args.kernels.split(",") if k]
         table: dict[str, dict[str, float]] = defaultdict(dict)
         names: list[str] = []
         for d in args.dirs:
@@ -136,6 +142,8 @@ def main(argv=None) -> int:
         print("| kernel | calls | average (us) | total (ms) | % |")
         print("|---|---|---|---|---|")
         for r in st:
+            if keep and not any(r["kernel"].startswith(p) for p in keep):
+                continue
             print(f"| `{r['kernel']}` | {r['calls']} | {r['avg_us']:.2f} | {r['total_ms']:.3f} | {r['pct']:.2f} |")
         return 0
 
@@ -158,7 +166,7 @@ def main(argv=None) -> int:
     print("| kernel | dispatches | fetch (MB) | write (MB) | fetch+write (MB) |")
     print("|---|---|---|---|---|")
     for k in fetch:
-        if k == copy:
+        if k == copy or (keep and not any(k.startswith(p) for p in keep)):
             continue
         fv = fetch[k]
         wv = write.get(k, [0.0])
