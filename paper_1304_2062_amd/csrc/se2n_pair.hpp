@@ -1340,7 +1340,7 @@ inline PairGeom pair_geom(int M, int N, int rsize, int num_cu) {
     return g;
 }
 
-// Launchers (se2n_pair_rows.hip, se2n_pair_mid.hip); spec holds N M/2 M
+// Launchers (se2n_pair_rows.hpp, se2n_pair_mid.hpp); spec holds N M/2 M
 // complex values.
 template <class R>
 hipError_t launch_pair_fwd(int src, const R* f, const uint8_t* mask, const uint8_t* rmap, const R* vol, C2<R>* spec,
